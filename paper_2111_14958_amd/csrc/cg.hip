@@ -48,30 +48,30 @@ namespace wd {
 // beta q (phaseA_tile with QR): solves that launch it (LaunchSet::qrec) have
 // no phase C; so do the even-odd phase-A kernels.
 // par >= 0: the fused finish (LaunchSet::fused): iteration parity par of the
-// chunk, first = 1 for the chunk's first iteration (see phaseA_tile); -1: the
-// three-launch iteration with k_finish after phase B.
+// chunk, first = 1 (phase A) for the chunk's first iteration, last = 1 (phase
+// B) for its last (see phaseA_tile, phaseB_tile); -1: the three-launch
+// iteration with k_finish after phase B.
 // MP: plane blocks of several z-adjacent planes (up to 512 threads).
 // Waves per SIMD asked of the register allocator: 3 for the FP64 kernels with
-// one rhs per thread (<= 168 VGPRs; left to the compiler it takes 172-182 for
-// some, which allows 2), except the two that would spill to reach it
-// (phase B with hop order 5, and site-blocked with hop order 3).
-template <int P, int NR, int ORD, bool XY, bool B>
+// one rhs per thread (<= 168 VGPRs; left to the compiler some take more, which
+// allows 2).
+template <int P, int NR>
 constexpr int phase_waves() {
-    return (P == P64 && NR == 1 && !(B && (ORD == 5 || (ORD == 3 && !XY)))) ? 3 : 1;
+    return P == P64 && NR == 1 ? 3 : 1;
 }
 
 template <int P, int NR, int ORD, bool XY, bool R12 = false, bool NT = false, bool MP = false>
-__global__ __launch_bounds__(MP ? 512 : 256, (phase_waves<P, NR, ORD, XY, false>())) void k_phaseA(
+__global__ __launch_bounds__(MP ? 512 : 256, (phase_waves<P, NR>())) void k_phaseA(
     const Prob *__restrict__ probs, int nprob, int remap, int par, int first) {
     WD_KERNEL_PROLOGUE(KA)
     phaseA_tile<P, NR, ORD, XY, R12, NT, true, MP>(pr, t_, par, first);
 }
 
 template <int P, int NR, int ORD, bool XY, bool R12 = false, bool NT = false, bool MP = false>
-__global__ __launch_bounds__(MP ? 512 : 256, (phase_waves<P, NR, ORD, XY, true>())) void k_phaseB(
-    const Prob *__restrict__ probs, int nprob, int remap, int par, int /*first*/) {
+__global__ __launch_bounds__(MP ? 512 : 256, (phase_waves<P, NR>())) void k_phaseB(
+    const Prob *__restrict__ probs, int nprob, int remap, int par, int last) {
     WD_KERNEL_PROLOGUE(KB)
-    phaseB_tile<P, NR, ORD, XY, R12, NT, true, MP>(pr, t_, par);
+    phaseB_tile<P, NR, ORD, XY, R12, NT, true, MP>(pr, t_, par, last);
 }
 
 // z-marching phases A and B (zm_tile); dynamic LDS of two plane buffers
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(1024) void k_finish(const Prob *__restrict__ probs,
         const Prob &pr = probs[j];
         if (kind & FIN_TRAIL) {
             const int pk = (kind >> 12) & 1;
-            phaseAB_finish(pr, pk ? pr.sc2 : pr.sc, pr.sc, pk ? 0 : 2);
+            phaseAB_finish(pr, pk ? pr.sc2 : pr.sc, pr.sc, pk ? 0 : 2, pk ? 0 : 1);
             continue;
         }
         switch (kind) {
@@ -445,11 +445,11 @@ static void launch_A(const KindShape &k, hipStream_t st, const Prob *d, int n, i
     else launch_AB_o<P, 1, false>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, first);
 }
 template <int P>
-static void launch_B(const KindShape &k, hipStream_t st, const Prob *d, int n, int par) {
-    if (k.ordered == 5) launch_AB_o5<P, true>(k.r12, k.nt, k.planes > 1, k.grid, k.block, st, d, n, k.remap, par, 0);
+static void launch_B(const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int last) {
+    if (k.ordered == 5) launch_AB_o5<P, true>(k.r12, k.nt, k.planes > 1, k.grid, k.block, st, d, n, k.remap, par, last);
     else if (k.ordered == 3)
-        launch_AB_o<P, 3, true>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, 0);
-    else launch_AB_o<P, 1, true>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, 0);
+        launch_AB_o<P, 3, true>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, last);
+    else launch_AB_o<P, 1, true>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, last);
 }
 template <int P, bool ZX = false>
 static void launch_R2(int nr, int xy, int grid, int blk, hipStream_t st, const Prob *d, int n, int remap) {
@@ -618,7 +618,7 @@ void launch_iterations(int inner, const LaunchSet &ls, hipStream_t st, const Pro
     if (ls.fused) {
         for (int it = 0; it < K; ++it) {
             launch_kind(KA, inner, ls, st, d, nprob, it & 1, it == 0);
-            launch_kind(KB, inner, ls, st, d, nprob, it & 1, 0);
+            launch_kind(KB, inner, ls, st, d, nprob, it & 1, it == K - 1);
         }
         hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, st, d, nprob, KB | FIN_AB | FIN_TRAIL | ((K & 1) << 12));
         return;
@@ -641,9 +641,9 @@ static void launch_kind_tiles(int kind, int inner, const KindShape &k, hipStream
         else launch_A<P16>(k, st, d, nprob, par, first);
         break;
     case KB:
-        if (inner == P64) launch_B<P64>(k, st, d, nprob, par);
-        else if (inner == P32) launch_B<P32>(k, st, d, nprob, par);
-        else launch_B<P16>(k, st, d, nprob, par);
+        if (inner == P64) launch_B<P64>(k, st, d, nprob, par, first);
+        else if (inner == P32) launch_B<P32>(k, st, d, nprob, par, first);
+        else launch_B<P16>(k, st, d, nprob, par, first);
         break;
     case KC:
         if (inner == P64 && k.nt) WD_TIMED_LAUNCH((k_phaseC<P64, true>), dim3(k.grid), dim3(k.block), st, d, nprob, 0);
@@ -1056,7 +1056,7 @@ static int profiled_chunk(int inner, const LaunchSet &ls, hipStream_t st, const 
                 t_ev_start = ev[6 * it + 2 * q];
                 t_ev_stop = ev[6 * it + 2 * q + 1];
                 if (ls.fused)   // the sequence launch_iterations records
-                    launch_kind_tiles(kinds[q], inner, ls.k[kinds[q]], st, dprob, 1, it & 1, q == 0 && it == 0);
+                    launch_kind_tiles(kinds[q], inner, ls.k[kinds[q]], st, dprob, 1, it & 1, it == (q == 0 ? 0 : K - 1));
                 else launch_kind_tiles(kinds[q], inner, ls.k[kinds[q]], st, dprob, 1);
                 t_ev_start = t_ev_stop = nullptr;
                 if (kinds[q] != KC && !ls.fused) launch_finish_after(kinds[q], ls, st, dprob, 1);
@@ -1082,7 +1082,10 @@ static int profiled_chunk(int inner, const LaunchSet &ls, hipStream_t st, const 
                 nc += it < d[i] - froze[i];
                 nq += it < d[i] && !(it == 0 && before[i].restart);   // phase A reads the old q
             }
-            const double bytes[3] = {G + nact * 2.0 * S + (ls.qrec ? nq * S : 0.0), G + nact * (3.0 * S + 2.0 * SX),
+            // phase B's x_lo: in every iteration, or with the fused finish two
+            // iterations' updates in the launches of parity 1 (which read both q)
+            const double bx = !ls.fused ? 2.0 * SX : (it & 1) ? S + 2.0 * SX : it == K - 1 ? 2.0 * SX : 0.0;
+            const double bytes[3] = {G + nact * 2.0 * S + (ls.qrec ? nq * S : 0.0), G + nact * (3.0 * S + bx),
                                      nc * 3.0 * S};
             const int cnt[3] = {nact, nact, ls.qrec ? 0 : nc};
             for (int k = 0; k < 3; ++k) {

@@ -56,7 +56,8 @@ struct alignas(16) Scal {
     int pending_p;    // 1: phase C must rebuild p for this rhs
     int restart;      // 1: the next direction is p = r
     int zero_src;     // 1: eta == 0, the solution is 0
-    int pad;
+    int xq;           // fused finish: bit 0 the buffer of the last q (0: pr.q, 1: pr.p), bit 1: x_lo
+                      // lacks the last iteration's alpha q (frozen half way through a pair)
 };
 
 // complex scalars of BiCGSTAB, one record per right-hand side
@@ -269,11 +270,13 @@ __device__ __forceinline__ unsigned rhs_mask(const Prob &pr, int rhs0, int want)
 // memory); store_fin writes them with the unchanged ones.
 struct Fin {
     double sigma, alpha, rho_old, rho, beta;
-    int state, iters, since_ru, pending_p;
+    int state, iters, since_ru, pending_p, xq;
 };
-__device__ __forceinline__ Fin cg_transition(const Prob &pr, const Scal &c0, double sigma, double rho) {
-    Fin f{c0.sigma, c0.alpha, c0.rho_old, c0.rho, c0.beta, c0.state, c0.iters, c0.since_ru, 0};
+// xq: the record's xq if the field iterated
+__device__ __forceinline__ Fin cg_transition(const Prob &pr, const Scal &c0, double sigma, double rho, int xq) {
+    Fin f{c0.sigma, c0.alpha, c0.rho_old, c0.rho, c0.beta, c0.state, c0.iters, c0.since_ru, 0, c0.xq};
     if (c0.state != ST_ACTIVE) return f;
+    f.xq = xq;
     f.sigma = sigma;
     if (!finite_pos(sigma)) {
         f.state = ST_BREAKDOWN;
@@ -309,7 +312,7 @@ __device__ __forceinline__ void store_fin(Scal &d, const Scal &c0, const Fin &f)
     d.pending_p = f.pending_p;
     d.restart = 0;
     d.zero_src = c0.zero_src;
-    d.pad = c0.pad;
+    d.xq = f.xq;
 }
 
 // ------------------------------------------------------------------ phase A
@@ -338,6 +341,10 @@ __device__ __forceinline__ void store_fin(Scal &d, const Scal &c0, const Fin &f)
 // records are final already (the reliable update or the trailing finish of the
 // chunk before wrote them) and are copied unchanged.  Partials go to slot 0
 // (par 0) or 2 (par 1).
+// With the fused finish q alternates between two buffers, pr.q (par 0) and
+// pr.p (par 1), so that phase B can add two iterations' alpha q to x_lo in one
+// pass (see phaseB_tile): the old q is read from the other buffer (in the
+// chunk's first iteration, from the one the field's record names).
 template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, bool NT = false, bool QR = false,
           bool MP = false>
 __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1, int first = 0) {
@@ -345,7 +352,7 @@ __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1,
     typedef typename LdsSpinor<P>::word W;
     __shared__ W xy[XY ? NR * LdsWords<P>::value * (MP ? 512 : 256) : 1];
     __shared__ double fsig[NR], frho[NR], fbeta[NR];
-    __shared__ int fact[NR], frestart[NR];
+    __shared__ int fact[NR], frestart[NR], foldq[NR];
     int sb, grp, s;
     stencil_tile<XY, MP>(pr, KA, t, sb, grp, s);
     const int rhs0 = grp * NR;
@@ -354,6 +361,7 @@ __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1,
     const Scal *sin = fused && par ? pr.sc2 : pr.sc;
     Scal *sout = par ? pr.sc : pr.sc2;
     const int wslot = fused && par ? 2 : 0;
+    const int xqn = par ? 2 : 1;   // xq of a field that iterated before this launch (parity par ^ 1)
     // fields that iterate before this launch's finish (uniform over the block)
     const unsigned act0 = rhs_mask<NR>(pr, sin, rhs0, ST_ACTIVE);
     double part[NR];
@@ -361,7 +369,7 @@ __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1,
     for (int j = 0; j < NR; ++j) part[j] = 0.0;
     const Geom g = pr.g;
     const int np = MP ? g.S[2] * xy_kp(pr.sorder[KA]) : g.S[2];   // sites staged in LDS
-    FieldPtr fp{QR ? pr.r : pr.p, g.V, pr.nrhs}, fq{pr.q, g.V, pr.nrhs};
+    FieldPtr fp{QR ? pr.r : pr.p, g.V, pr.nrhs}, fq{fused && par ? pr.p : pr.q, g.V, pr.nrhs};
     // the fields of this launch's records that the finish's decision reads,
     // loaded early by the thread that decides, so the staging covers the latency
     Scal c0[NR];
@@ -377,6 +385,7 @@ __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1,
             c0[j].since_ru = m.since_ru;
             c0[j].beta = m.beta;
             c0[j].restart = m.restart;
+            c0[j].xq = m.xq;
         }
     }
     double as[NR][4], ar[NR][4];
@@ -406,14 +415,16 @@ __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1,
             for (int j = 0; j < NR; ++j) {
                 const bool live = act0 >> j & 1;
                 if (fin) {
-                    const Fin f = cg_transition(pr, c0[j], live ? fsig[j] : 0.0, live ? frho[j] : 0.0);
+                    const Fin f = cg_transition(pr, c0[j], live ? fsig[j] : 0.0, live ? frho[j] : 0.0, xqn);
                     fact[j] = live && f.state == ST_ACTIVE;
                     fbeta[j] = f.beta;
                     frestart[j] = 0;
+                    foldq[j] = par ^ 1;
                 } else {
                     fact[j] = live;
                     fbeta[j] = c0[j].beta;
                     frestart[j] = c0[j].restart;
+                    foldq[j] = c0[j].xq & 1;
                 }
             }
         __syncthreads();
@@ -437,8 +448,9 @@ __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1,
                 if constexpr (QR) {
                     if (!(fused ? frestart[j] : pr.sc[rhs0 + j].restart)) {
                         const R b = (R)(fused ? fbeta[j] : pr.sc[rhs0 + j].beta);
+                        const FieldPtr fo{fused && foldq[j] ? pr.p : pr.q, g.V, pr.nrhs};
                         cx<R> qo[12];
-                        Spinor<P>::template load<NT>(fq, rhs0 + j, s, qo);
+                        Spinor<P>::template load<NT>(fo, rhs0 + j, s, qo);
 #pragma unroll
                         for (int k = 0; k < 12; ++k) o[k] = {o[k].re + b * qo[k].re, o[k].im + b * qo[k].im};
                     }
@@ -467,7 +479,8 @@ __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1,
                 const Scal full = sin[rhs0 + j];
                 if (fin) {
                     const bool live = act0 >> j & 1;
-                    store_fin(sout[rhs0 + j], full, cg_transition(pr, full, live ? fsig[j] : 0.0, live ? frho[j] : 0.0));
+                    store_fin(sout[rhs0 + j], full,
+                              cg_transition(pr, full, live ? fsig[j] : 0.0, live ? frho[j] : 0.0, xqn));
                 } else {
                     sout[rhs0 + j] = full;
                 }
@@ -565,9 +578,21 @@ __device__ __forceinline__ void fa_reduce(const Prob &pr, int rhs0, unsigned act
 // par >= 0 (with FA; the fused finish, see phaseA_tile): the records are those
 // the phase-A launch of iteration parity par wrote (pr.sc2 for par 0, pr.sc for
 // 1) and phase A's partials are in slot 0 (par 0) or 2 (par 1).
+// x_lo is not needed inside the iteration, so with the fused finish it is
+// updated in every second one: the launch of parity 1 adds the iteration
+// before's alpha q (the other q buffer, the record's alpha) and then its own,
+// in the order and with the roundings of two single updates, so the solution
+// is bitwise the same.  A pair of iterations reads one q more and moves x_lo
+// twice less per field: of phase B's 5 spinor streams half a one.  Phase B is
+// bound by what it moves through the fabric (6.5 TB/s at 14^4 x 16, FP32): mean
+// launch 70.1 -> 64.3 us, whole solves at 14^4 x 16 FP32 16.1 -> 15.5 ms, 12^4
+// x 12 FP64 14.0 -> 13.4 ms, 16^3 x 32 x 12 FP16N (whose x_lo is FP32) 35.1 ->
+// 33.2 ms; a single 8^4 field, bound by latency, 2.08 -> 2.10 ms.  last = 1
+// (the chunk's last iteration): parity 0 adds its own alpha q at once.  A field that freezes after a parity-0 iteration keeps
+// its pending alpha q (xq bit 1) for R1.
 template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, bool NT = false, bool FA = false,
           bool MP = false>
-__device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1) {
+__device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1, int last = 0) {
     typedef typename real_of<P>::type R;
     constexpr int XP = XPrec<P>::value;
     typedef typename real_of<XP>::type RX;
@@ -585,7 +610,8 @@ __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1)
     for (int j = 0; j < NR; ++j) part[j] = 0.0;
     const Geom g = pr.g;
     const int np = MP ? g.S[2] * xy_kp(pr.sorder[KB]) : g.S[2];   // sites staged in LDS
-    FieldPtr fq{pr.q, g.V, pr.nrhs}, fr{pr.r, g.V, pr.nrhs}, fx{pr.x_lo, g.V, pr.nrhs};
+    FieldPtr fq{par > 0 ? pr.p : pr.q, g.V, pr.nrhs}, fr{pr.r, g.V, pr.nrhs}, fx{pr.x_lo, g.V, pr.nrhs};
+    const bool xup = par != 0 || last;   // this launch updates x_lo
     if constexpr (FA) {
         if (act) {   // uniform over the block
             double a[NR][4];
@@ -626,8 +652,27 @@ __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1)
 #pragma unroll
                 for (int k = 0; k < 12; ++k) n += (double)norm2(r[k]);
                 part[j] = n;
+                if (!xup) continue;
+                // issued once r is done with (no instruction): three more
+                // spinors loaded ahead of it would cost phase B a wave per SIMD
+                int sx = s;
+                asm volatile("" : "+v"(sx) : "v"(n));
                 cx<RX> x[12];
-                Spinor<XP>::template load<NT>(fx, rhs0 + j, s, x);
+                Spinor<XP>::template load<NT>(fx, rhs0 + j, sx, x);
+                if (par > 0) {   // the iteration before's update first
+                    const FieldPtr fo{pr.q, g.V, pr.nrhs};
+                    const RX ao = (RX)sc[rhs0 + j].alpha;
+                    cx<R> qo[12];
+                    Spinor<P>::template load<NT>(fo, rhs0 + j, sx, qo);
+#pragma unroll
+                    for (int k = 0; k < 12; ++k) x[k] = {x[k].re + ao * (RX)qo[k].re, x[k].im + ao * (RX)qo[k].im};
+                }
+                // q read again (from LDS, or a line this thread has just read), so
+                // that it is not held meanwhile
+                int tx = XY ? (int)threadIdx.x : sx;
+                asm volatile("" : "+v"(tx) : "v"(x[0].re), "v"(x[11].im));
+                if constexpr (XY) LdsSpinor<P>::get(xy, np, j, tx, q);
+                else Spinor<P>::load(fq, rhs0 + j, tx, q);
                 const RX ax = (RX)al;
 #pragma unroll
                 for (int k = 0; k < 12; ++k) x[k] = {x[k].re + ax * (RX)q[k].re, x[k].im + ax * (RX)q[k].im};
@@ -706,19 +751,20 @@ __device__ __forceinline__ void sum_ab(const Prob &pr, double *sa, double *sb, i
 // followed by phaseB_finish give.  The records are read from sin and written
 // to sout (the same array in the three-launch iteration; with the fused
 // finish, the chunk's last records into pr.sc).
-__device__ __forceinline__ void phaseAB_finish(const Prob &pr, const Scal *sin, Scal *sout, int aslot) {
+// xq: see Scal.
+__device__ __forceinline__ void phaseAB_finish(const Prob &pr, const Scal *sin, Scal *sout, int aslot, int xq) {
     __shared__ double sa[MAX_SUMS], sbb[MAX_SUMS];
     const int i = threadIdx.x;
     Scal c0;
     if (i < pr.nrhs) c0 = sin[i];
     if (!__syncthreads_or(i < pr.nrhs && c0.state == ST_ACTIVE)) {   // nothing to sum
-        if (i < pr.nrhs) store_fin(sout[i], c0, cg_transition(pr, c0, 0.0, 0.0));
+        if (i < pr.nrhs) store_fin(sout[i], c0, cg_transition(pr, c0, 0.0, 0.0, xq));
         return;
     }
     sum_ab(pr, sa, sbb, aslot);
-    if (i < pr.nrhs) store_fin(sout[i], c0, cg_transition(pr, c0, sa[i], sbb[i]));
+    if (i < pr.nrhs) store_fin(sout[i], c0, cg_transition(pr, c0, sa[i], sbb[i], xq));
 }
-__device__ __forceinline__ void phaseAB_finish(const Prob &pr) { phaseAB_finish(pr, pr.sc, pr.sc, 0); }
+__device__ __forceinline__ void phaseAB_finish(const Prob &pr) { phaseAB_finish(pr, pr.sc, pr.sc, 0, 0); }
 
 // ---------------------------------------------- z-marching phases A and B
 // A tile is a column of xy-planes: one t, one rhs, the planes z0 <= z < z1 of
@@ -837,7 +883,8 @@ __device__ __forceinline__ void phaseC_tile(const Prob &pr, int t) {
 }
 
 // ------------------------------------------------------- reliable update R1
-// x64 += x_lo; x_lo = 0   (rhs that are frozen)
+// x64 += x_lo; x_lo = 0   (rhs that are frozen; x_lo + alpha q for a field whose
+// last update is pending, see phaseB_tile)
 template <int P>
 __device__ __forceinline__ void ru1_tile(const Prob &pr, int t) {
     constexpr int XP = XPrec<P>::value;
@@ -850,6 +897,15 @@ __device__ __forceinline__ void ru1_tile(const Prob &pr, int t) {
     cx<double> x[12];
     Spinor<XP>::load(fx, i, s, xl);
     Spinor<P64>::load(f64, i, s, x);
+    if (pr.sc[i].xq & 2) {
+        typedef typename real_of<P>::type R;
+        const FieldPtr fq{pr.q, pr.vf, pr.nrhs};
+        const RX a = (RX)pr.sc[i].alpha;
+        cx<R> q[12];
+        Spinor<P>::load(fq, i, s, q);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) xl[k] = {xl[k].re + a * (RX)q[k].re, xl[k].im + a * (RX)q[k].im};
+    }
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
         x[k] = {x[k].re + (double)xl[k].re, x[k].im + (double)xl[k].im};
@@ -939,6 +995,7 @@ __device__ __forceinline__ void ru2_finish(const Prob &pr) {
             c.n_ru += 1;
             c.since_ru = 0;
             c.pending_p = 0;
+            c.xq &= 1;
             if (r2 <= c.stop2) c.state = ST_DONE;
             else if (!(r2 < 1e300)) c.state = ST_BREAKDOWN;
             else if (c.iters >= pr.max_iter) c.state = ST_NOTCONV;

@@ -50,8 +50,9 @@ void plan_persistent(LaunchSet &ls, Prob &pr, int64_t V, int nrhs, int inner, in
 void fill_prob(Prob &pr, const wd_gauge *g, double m0, int nrhs, const wd_cg_params &p, char *ws,
                const WsLayout &L);
 void init_scalars(std::vector<Scal> &sc, int nrhs);
-// One kernel kind of a CG iteration (and the finish after it).  par >= 0, first:
-// phase A or B of a fused-finish iteration (see launch_iterations).
+// One kernel kind of a CG iteration (and the finish after it).  par >= 0: phase
+// A or B of a fused-finish iteration (see launch_iterations); first: phase A of
+// a chunk's first iteration, phase B of its last.
 void launch_kind(int kind, int inner, const LaunchSet &ls, hipStream_t st, const Prob *d, int nprob, int par = -1,
                  int first = 0);
 // the first true residual of a solve; x_zero: x64 is zero (no stencil needed)
