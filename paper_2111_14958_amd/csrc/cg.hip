@@ -1414,7 +1414,7 @@ int wd_tune_cg(const wd_gauge *g, double m0, int32_t inner, const void *src, int
                 for (int strip : {4, 0, 2, 7}) {
                     if (strip >= Lz) continue;
                     if (ord == 5 && !(xy && nr == 1)) continue;   // memory hops first: plane blocks
-                    Shape s = default_shape(inner, nrhs, FAM_CG_B);
+                    Shape s = default_shape(kb);
                     s.block = 256;
                     s.nr = nr;
                     s.ordered = ord;

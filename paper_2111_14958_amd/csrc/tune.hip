@@ -46,8 +46,8 @@ static bool g_loaded = false;
 // sites (else the site-blocked kernels).  One rhs per thread everywhere.
 // Operator kernel: plane-blocked, two z-adjacent planes per block in FP32
 // with 8 or more rhs.
-// CG phase kernels: plane-blocked (one plane per block) in FP32 and FP64; in
-// FP16N the site-blocked kernel is faster.  The reliable-update kernel:
+// CG phase kernels: plane-blocked in FP32 and FP64, one plane per block or two
+// (cg_two_planes); in FP16N by fp16_planes.  The reliable-update kernel:
 // plane-blocked.
 // wd_tune_result.site_order: strip | planes per block << 12 (0: one) |
 // group-major << 16 | plane-blocked << 17 | blocks-per-CU cap << 18 |
@@ -57,7 +57,37 @@ int encode_order(const Shape &s) {
            (s.occ << 18) | ((s.xylds == 2) << 24) | (s.fpass << 25);
 }
 
-Shape default_shape(int prec, int nrhs, int fam) {
+// FP16N phases A and B on plane blocks rather than site blocks.  The decoding
+// and coding of FP16N make the phases bound by issue as much as by memory, so
+// lanes left idle by a plane that does not fill its wavefronts cost more than
+// the x and y neighbours from LDS save: planes of more than 128 sites, 7/8 of
+// the lanes in use, and three blocks or more per compute unit.  Whole solves,
+// site against plane blocks: 16 x 16 planes (16^3 x 32, 12 fields) 33.4 -> 30.8
+// ms, 13 x 14 (16 x 24 of them, 4 fields) 7.6 -> 6.9 ms; but 14 x 14 (196 of
+// 256 lanes; 14^4, 16 fields) 12.4 -> 12.9 ms, 16 x 12 (192 planes, 3 fields)
+// 3.9 -> 4.3 ms.  One field is bound by latency, where planes win at every
+// size (8^4 2.6 -> 2.5 ms, 12^4 2.9 -> 2.6 ms, 14^4 3.0 -> 2.9 ms).
+static bool fp16_planes(const int L[4], int nrhs) {
+    const int np = L[0] * L[1], lanes = (np + 63) / 64 * 64;
+    const int64_t blocks = (int64_t)L[2] * L[3] * nrhs;
+    return nrhs == 1 || (np > 128 && 8 * np >= 7 * lanes && blocks >= 768);
+}
+
+// Planes per block of phases A and B (FP32, FP16N): two where a plane has 256
+// sites, so that 512-thread blocks have no idle lane and three of them fill a
+// compute unit's wavefronts, if the blocks come in whole rounds of the 256
+// compute units or there are four rounds or more.  Whole solves, one plane
+// against two: 16^3 x 32 FP16N 1 / 2 / 12 fields 5.0 -> 4.5, 6.8 -> 6.2, 30.8
+// -> 30.0 ms, FP32 1 / 4 / 8 fields 5.3 -> 4.8, 14.7 -> 13.9, 29.8 -> 28.7 ms;
+// but 16^4 with 1 and 3 fields (a half and one and a half rounds) FP32 3.5 ->
+// 3.7, 5.6 -> 6.1 ms, and planes of 240 or 224 sites gain nothing.
+static bool cg_two_planes(const int L[4], int nrhs) {
+    const int64_t blocks = (int64_t)L[2] * L[3] * nrhs / 2;
+    return L[0] * L[1] == 256 && L[2] % 2 == 0 && (blocks % 256 == 0 || blocks >= 1024);
+}
+
+Shape default_shape(const ShapeKey &k) {
+    const int prec = k.prec, nrhs = k.nrhs, fam = k.fam;
     Shape s;
     s.block = 256;
     s.remap = 1;
@@ -85,13 +115,19 @@ Shape default_shape(int prec, int nrhs, int fam) {
         s.xylds = 1;
     } else {
         s.nr = 1;
-        s.xylds = prec != WD_F16N;
+        s.xylds = prec != WD_F16N || fp16_planes(k.L, nrhs);
         // FP64: strips of 2 z-planes measured faster than 4 at 14^4, 16 rhs
         // (phase B 6 %; the whole solve 3 % more with phase A's too)
         if (prec == WD_F64) s.strip = 2;
         // plane blocks with the memory hops first: FP32 phase A 57.0 -> 53.4 us,
         // phase B 71.7 -> 69.5 us; FP64 phase A 112.8 -> 109.7 us
         if (s.xylds) s.ordered = 5;
+        if (s.xylds && prec != WD_F64 && cg_two_planes(k.L, nrhs)) {
+            s.planes = 2;
+            // wider strips with few fields (16^3 x 32, 2 fields, FP32: 8.0 -> 7.6
+            // ms; 12 fields, FP16N: 28.8 -> 29.6 ms)
+            s.strip = nrhs <= 4 ? 8 : 4;
+        }
     }
     return s;
 }
@@ -147,7 +183,7 @@ Shape shape_lookup(const ShapeKey &k) {
     load_cache_locked();
     auto it = g_table.find(k);
     if (it != g_table.end()) return it->second.first;
-    return default_shape(k.prec, k.nrhs, k.fam);
+    return default_shape(k);
 }
 
 void shape_store(const ShapeKey &k, const Shape &s) {
