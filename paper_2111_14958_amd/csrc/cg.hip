@@ -115,29 +115,32 @@ __global__ __launch_bounds__(256) void k_norm(const Prob *__restrict__ probs, in
 // Even-odd preconditioning (eo_core.h)
 // XY: half-plane blocks (see eo_tile), hop order 5, one rhs per thread
 template <int P, int NR, bool DAG, bool R12 = false, bool XY = false>
-__global__ __launch_bounds__(256) void k_eo_hop1(const Prob *__restrict__ probs, int nprob, int remap) {
+__global__ __launch_bounds__(256) void k_eo_hop1(const Prob *__restrict__ probs, int nprob, int remap, int par, int /*edge*/) {
     WD_KERNEL_PROLOGUE(DAG ? KEA1 : KEB1)
-    eo_hop1_tile<P, NR, DAG, true, R12, XY>(pr, t_);
+    eo_hop1_tile<P, NR, DAG, true, R12, XY>(pr, t_, par);
 }
 template <int P, int NR, bool R12 = false, bool XY = false>
-__global__ __launch_bounds__(256) void k_eo_phaseA(const Prob *__restrict__ probs, int nprob, int remap) {
+__global__ __launch_bounds__(256) void k_eo_phaseA(const Prob *__restrict__ probs, int nprob, int remap, int par, int edge) {
     WD_KERNEL_PROLOGUE(KA)
-    eo_phaseA_tile<P, NR, true, R12, XY>(pr, t_);
+    eo_phaseA_tile<P, NR, true, R12, XY>(pr, t_, par, edge);
 }
+// Waves per SIMD asked of the register allocator for the half-plane variant in
+// FP16N, which left to itself takes 103 VGPRs (4 waves; FP32 76-81, FP64 127)
+template <int P, int NR, bool XY> constexpr int eo_phaseB_waves() { return XY && NR == 1 && P == P16 ? 5 : 1; }
 template <int P, int NR, bool R12 = false, bool XY = false>
-__global__ __launch_bounds__(256) void k_eo_phaseB(const Prob *__restrict__ probs, int nprob, int remap) {
+__global__ __launch_bounds__(256, (eo_phaseB_waves<P, NR, XY>())) void k_eo_phaseB(const Prob *__restrict__ probs, int nprob, int remap, int par, int edge) {
     WD_KERNEL_PROLOGUE(KB)
-    eo_phaseB_tile<P, NR, R12, XY>(pr, t_);
+    eo_phaseB_tile<P, NR, R12, XY>(pr, t_, par, edge);
 }
 template <int NR>
 __global__ __launch_bounds__(256) void k_eo_ru2a(const Prob *__restrict__ probs, int nprob, int remap) {
     WD_KERNEL_PROLOGUE(KER2A)
     eo_ru2a_tile<NR>(pr, t_);
 }
-template <int P, int NR>
+template <int P, int NR, bool ZX = false>
 __global__ __launch_bounds__(256) void k_eo_ru2b(const Prob *__restrict__ probs, int nprob, int remap) {
     WD_KERNEL_PROLOGUE(KR2)
-    eo_ru2b_tile<P, NR>(pr, t_);
+    eo_ru2b_tile<P, NR, ZX>(pr, t_);
 }
 __global__ __launch_bounds__(256) void k_eo_source(const Prob *__restrict__ probs) {
     eo_source_tile(probs[0], (int)blockIdx.x);
@@ -500,82 +503,40 @@ static void launch_finish_after(int kind, const LaunchSet &ls, hipStream_t st, c
     launch_finish(kind == KB && fa ? (KB | FIN_AB) : kind, st, d, nprob);
 }
 
-// the half-plane blocked hops of phases A and B (one rhs per thread; FP32 on
-// the reconstruct-12 links where the gauge has them)
-template <int P, bool R12>
-static void launch_eo_xy(int kind, const KindShape &k, hipStream_t st, const Prob *d, int n) {
+// The even-odd hops of phases A and B, one kernel of the kind with the template
+// arguments given (links R12, half-plane blocks XY).  par, edge: as for
+// k_phaseA and k_phaseB.
+template <int P, int NR, bool R12, bool XY>
+static void launch_eo_AB(int kind, const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int edge) {
     const dim3 gr(k.grid), bl(k.block);
-    const size_t lds = k.lds;   // the half-plane's spinors
+    const size_t lds = XY ? k.lds : 0;   // the half-plane's spinors
     switch (kind) {
-    case KEA1: hipLaunchKernelGGL((k_eo_hop1<P, 1, true, R12, true>), gr, bl, lds, st, d, n, k.remap); break;
-    case KEB1: hipLaunchKernelGGL((k_eo_hop1<P, 1, false, R12, true>), gr, bl, lds, st, d, n, k.remap); break;
-    case KA: hipLaunchKernelGGL((k_eo_phaseA<P, 1, R12, true>), gr, bl, lds, st, d, n, k.remap); break;
-    case KB: hipLaunchKernelGGL((k_eo_phaseB<P, 1, R12, true>), gr, bl, lds, st, d, n, k.remap); break;
+    case KEA1: hipLaunchKernelGGL((k_eo_hop1<P, NR, true, R12, XY>), gr, bl, lds, st, d, n, k.remap, par, edge); break;
+    case KEB1: hipLaunchKernelGGL((k_eo_hop1<P, NR, false, R12, XY>), gr, bl, lds, st, d, n, k.remap, par, edge); break;
+    case KA: hipLaunchKernelGGL((k_eo_phaseA<P, NR, R12, XY>), gr, bl, lds, st, d, n, k.remap, par, edge); break;
+    case KB: hipLaunchKernelGGL((k_eo_phaseB<P, NR, R12, XY>), gr, bl, lds, st, d, n, k.remap, par, edge); break;
     }
 }
-// the FP32 half-lattice hops of phases A and B on the reconstruct-12 links
-static void launch_eo_r12(int kind, const KindShape &k, hipStream_t st, const Prob *d, int n) {
-    const dim3 gr(k.grid), bl(k.block);
-    const bool two = k.nr >= 2;
-    switch (kind) {
-    case KEA1:
-        if (two) hipLaunchKernelGGL((k_eo_hop1<P32, 2, true, true>), gr, bl, 0, st, d, n, k.remap);
-        else hipLaunchKernelGGL((k_eo_hop1<P32, 1, true, true>), gr, bl, 0, st, d, n, k.remap);
-        break;
-    case KEB1:
-        if (two) hipLaunchKernelGGL((k_eo_hop1<P32, 2, false, true>), gr, bl, 0, st, d, n, k.remap);
-        else hipLaunchKernelGGL((k_eo_hop1<P32, 1, false, true>), gr, bl, 0, st, d, n, k.remap);
-        break;
-    case KA:
-        if (two) hipLaunchKernelGGL((k_eo_phaseA<P32, 2, true>), gr, bl, 0, st, d, n, k.remap);
-        else hipLaunchKernelGGL((k_eo_phaseA<P32, 1, true>), gr, bl, 0, st, d, n, k.remap);
-        break;
-    case KB:
-        if (two) hipLaunchKernelGGL((k_eo_phaseB<P32, 2, true>), gr, bl, 0, st, d, n, k.remap);
-        else hipLaunchKernelGGL((k_eo_phaseB<P32, 1, true>), gr, bl, 0, st, d, n, k.remap);
-        break;
-    }
-}
-// even-odd kernels of the stencil kinds (site blocks: 1 or 2 rhs per thread;
-// half-plane blocks: launch_eo_xy)
+// even-odd kernels of the stencil kinds: half-plane blocks (one rhs per thread)
+// or site blocks (1 or 2); the reconstruct-12 links in FP32 where the gauge has them
 template <int P>
-static void launch_eo(int kind, const KindShape &k, hipStream_t st, const Prob *d, int n) {
+static void launch_eo(int kind, const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int edge) {
     const dim3 gr(k.grid), bl(k.block);
     const bool two = k.nr >= 2;
-    if (k.xy && (kind == KEA1 || kind == KEB1 || kind == KA || kind == KB)) {
-        if (P == P32 && k.r12) launch_eo_xy<P, P == P32>(kind, k, st, d, n);   // R12: FP32 only
-        else launch_eo_xy<P, false>(kind, k, st, d, n);
-        return;
-    }
-    if (P == P32 && k.r12 && (kind == KEA1 || kind == KEB1 || kind == KA || kind == KB)) {
-        launch_eo_r12(kind, k, st, d, n);
-        return;
-    }
-    switch (kind) {
-    case KEA1:
-        if (two) hipLaunchKernelGGL((k_eo_hop1<P, 2, true>), gr, bl, 0, st, d, n, k.remap);
-        else hipLaunchKernelGGL((k_eo_hop1<P, 1, true>), gr, bl, 0, st, d, n, k.remap);
-        break;
-    case KEB1:
-        if (two) hipLaunchKernelGGL((k_eo_hop1<P, 2, false>), gr, bl, 0, st, d, n, k.remap);
-        else hipLaunchKernelGGL((k_eo_hop1<P, 1, false>), gr, bl, 0, st, d, n, k.remap);
-        break;
-    case KA:
-        if (two) hipLaunchKernelGGL((k_eo_phaseA<P, 2>), gr, bl, 0, st, d, n, k.remap);
-        else hipLaunchKernelGGL((k_eo_phaseA<P, 1>), gr, bl, 0, st, d, n, k.remap);
-        break;
-    case KB:
-        if (two) hipLaunchKernelGGL((k_eo_phaseB<P, 2>), gr, bl, 0, st, d, n, k.remap);
-        else hipLaunchKernelGGL((k_eo_phaseB<P, 1>), gr, bl, 0, st, d, n, k.remap);
-        break;
-    case KER2A:
+    if (kind == KER2A) {
         if (two) hipLaunchKernelGGL((k_eo_ru2a<2>), gr, bl, 0, st, d, n, k.remap);
         else hipLaunchKernelGGL((k_eo_ru2a<1>), gr, bl, 0, st, d, n, k.remap);
-        break;
-    case KR2:
+    } else if (kind == KR2) {
         if (two) hipLaunchKernelGGL((k_eo_ru2b<P, 2>), gr, bl, 0, st, d, n, k.remap);
         else hipLaunchKernelGGL((k_eo_ru2b<P, 1>), gr, bl, 0, st, d, n, k.remap);
-        break;
+    } else if (P == P32 && k.r12) {   // R12: FP32 only
+        if (k.xy) launch_eo_AB<P, 1, P == P32, true>(kind, k, st, d, n, par, edge);
+        else if (two) launch_eo_AB<P, 2, P == P32, false>(kind, k, st, d, n, par, edge);
+        else launch_eo_AB<P, 1, P == P32, false>(kind, k, st, d, n, par, edge);
+    } else {
+        if (k.xy) launch_eo_AB<P, 1, false, true>(kind, k, st, d, n, par, edge);
+        else if (two) launch_eo_AB<P, 2, false, false>(kind, k, st, d, n, par, edge);
+        else launch_eo_AB<P, 1, false, false>(kind, k, st, d, n, par, edge);
     }
 }
 
@@ -588,9 +549,9 @@ void launch_kind(int kind, int inner, const LaunchSet &ls, hipStream_t st, const
                          kind == KS5;
     const bool eo_kind = kind == KA || kind == KB || kind == KR2 || kind == KEA1 || kind == KEB1 || kind == KER2A;
     if (ls.eo && eo_kind) {
-        if (inner == P64) launch_eo<P64>(kind, k, st, d, nprob);
-        else if (inner == P32) launch_eo<P32>(kind, k, st, d, nprob);
-        else launch_eo<P16>(kind, k, st, d, nprob);
+        if (inner == P64) launch_eo<P64>(kind, k, st, d, nprob, par, first);
+        else if (inner == P32) launch_eo<P32>(kind, k, st, d, nprob, par, first);
+        else launch_eo<P16>(kind, k, st, d, nprob, par, first);
     } else {
         launch_kind_tiles(kind, inner, k, st, d, nprob, par, first);
     }
@@ -602,12 +563,25 @@ void launch_kind(int kind, int inner, const LaunchSet &ls, hipStream_t st, const
 // The first true residual of a solve (R2).  x_zero: x64 is zero (no initial
 // guess), so r = eta is formed without the FP64 stencil (bitwise the same).
 void launch_first_residual(int inner, const LaunchSet &ls, hipStream_t st, const Prob *d, int nprob, bool x_zero) {
-    if (!x_zero || ls.eo) {
+    if (!x_zero) {
+        if (ls.eo) launch_kind(KER2A, inner, ls, st, d, nprob);
         launch_kind(KR2, inner, ls, st, d, nprob);
         return;
     }
     const KindShape &k = ls.k[KR2];
     if (k.grid <= 0) return;
+    if (ls.eo) {   // one rhs per thread: nothing shared between fields without the hops
+        const dim3 gr(k.grid), bl(k.block);
+        const bool two = k.nr >= 2;
+        auto zx = [&](auto one, auto pair) {
+            hipLaunchKernelGGL(two ? pair : one, gr, bl, 0, st, d, nprob, k.remap);
+        };
+        if (inner == P64) zx(k_eo_ru2b<P64, 1, true>, k_eo_ru2b<P64, 2, true>);
+        else if (inner == P32) zx(k_eo_ru2b<P32, 1, true>, k_eo_ru2b<P32, 2, true>);
+        else zx(k_eo_ru2b<P16, 1, true>, k_eo_ru2b<P16, 2, true>);
+        launch_finish(KR2, st, d, nprob);
+        return;
+    }
     if (inner == P64) launch_R2<P64, true>(k.nr, k.xy, k.grid, k.block, st, d, nprob, k.remap);
     else if (inner == P32) launch_R2<P32, true>(k.nr, k.xy, k.grid, k.block, st, d, nprob, k.remap);
     else launch_R2<P16, true>(k.nr, k.xy, k.grid, k.block, st, d, nprob, k.remap);
@@ -617,7 +591,9 @@ void launch_first_residual(int inner, const LaunchSet &ls, hipStream_t st, const
 void launch_iterations(int inner, const LaunchSet &ls, hipStream_t st, const Prob *d, int nprob, int K) {
     if (ls.fused) {
         for (int it = 0; it < K; ++it) {
+            if (ls.eo) launch_kind(KEA1, inner, ls, st, d, nprob, it & 1, 0);
             launch_kind(KA, inner, ls, st, d, nprob, it & 1, it == 0);
+            if (ls.eo) launch_kind(KEB1, inner, ls, st, d, nprob, it & 1, 0);
             launch_kind(KB, inner, ls, st, d, nprob, it & 1, it == K - 1);
         }
         hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, st, d, nprob, KB | FIN_AB | FIN_TRAIL | ((K & 1) << 12));
@@ -847,10 +823,10 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
     // direction as q
     ls.qrec = ls.eo || ls.k[KA].xy != 2;
     // phase A completes the previous iteration's finish: plane or site blocks
-    // with phase A's reduction inside phase B (not even-odd, not z-marching).
-    // WD_CG_UNFUSED=1 selects the three-launch iteration instead (the same
-    // arithmetic; kept for comparisons).
-    ls.fused = !ls.eo && ls.k[KA].xy != 2 && ls.k[KB].xy != 2 && !unfused_requested();
+    // with phase A's reduction inside phase B, even-odd or not (not
+    // z-marching).  WD_CG_UNFUSED=1 selects the iteration with finish launches
+    // instead (the same arithmetic; kept for comparisons).
+    ls.fused = ls.k[KA].xy != 2 && ls.k[KB].xy != 2 && !unfused_requested();
 }
 
 // The persistent kernel runs phases A and B with one block shape, site blocks
@@ -1186,7 +1162,6 @@ int cg_run(const wd_gauge *g, double m0, const void *src, void *sol, int nrhs, c
     launch_kind(KN, p.inner, ls, st, dprob, 1);
     if (eo) {
         launch_eo_source(dprob, Vf, nrhs, st);
-        launch_kind(KER2A, p.inner, ls, st, dprob, 1);
     }
     launch_first_residual(p.inner, ls, st, dprob, 1, !p.use_x0);
     if (!bicg) launch_kind(KC, p.inner, ls, st, dprob, 1);

@@ -315,214 +315,10 @@ __device__ __forceinline__ void store_fin(Scal &d, const Scal &c0, const Fin &f)
     d.xq = f.xq;
 }
 
-// ------------------------------------------------------------------ phase A
-// q = D^dagger p for active rhs; partial |q|^2 (of the stored q)
-// XY: plane-blocked (one xy-plane per block, x/y neighbours from LDS).
-// MP (with XY): several z-adjacent planes per block (stencil_tile).  All z
-// neighbours still come from memory: reading the ones inside the block from
-// LDS (a branch per lane) took phases A and B from 77 to 95 VGPRs and 6 to 5
-// waves per SIMD.
-// R12: the links are the gauge's reconstruct-12 copy pr.U12 (two rows per link).
-// QR: the direction is carried as q alone.  Since p = r + beta p_old, its image
-// q = D^dagger p is D^dagger r + beta q_old: the stencil reads r and each site
-// adds beta times its own old q (q = D^dagger r after a restart), so neither p
-// nor a pass forming it (phase C) is needed.  Only the site's own q is read,
-// so q is updated in place.
-//
-// Fused finish (par >= 0, with QR): the launch also completes the finish of the
-// iteration before it, so an iteration is two launches.  Every block sums, for
-// its own fields and in the finish's fixed order, phase A's partials of the
-// previous iteration (slot 2 for par 0, slot 0 for par 1) and phase B's (slot
-// 1), and applies the same transition (cg_transition) to the records it reads
-// from pr.sc (par 0) or pr.sc2 (par 1); the site block 0 of each field group
-// writes the results to the other array, which no block of this launch reads.
-// So every block gets the same alpha, beta and state, bitwise equal to what
-// k_finish would have recorded.  first = 1 (the chunk's first iteration): the
-// records are final already (the reliable update or the trailing finish of the
-// chunk before wrote them) and are copied unchanged.  Partials go to slot 0
-// (par 0) or 2 (par 1).
-// With the fused finish q alternates between two buffers, pr.q (par 0) and
-// pr.p (par 1), so that phase B can add two iterations' alpha q to x_lo in one
-// pass (see phaseB_tile): the old q is read from the other buffer (in the
-// chunk's first iteration, from the one the field's record names).
-template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, bool NT = false, bool QR = false,
-          bool MP = false>
-__device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1, int first = 0) {
-    typedef typename real_of<P>::type R;
-    typedef typename LdsSpinor<P>::word W;
-    __shared__ W xy[XY ? NR * LdsWords<P>::value * (MP ? 512 : 256) : 1];
-    __shared__ double fsig[NR], frho[NR], fbeta[NR];
-    __shared__ int fact[NR], frestart[NR], foldq[NR];
-    int sb, grp, s;
-    stencil_tile<XY, MP>(pr, KA, t, sb, grp, s);
-    const int rhs0 = grp * NR;
-    const bool fused = QR && par >= 0;   // uniform over the launch
-    const bool fin = fused && !first;
-    const Scal *sin = fused && par ? pr.sc2 : pr.sc;
-    Scal *sout = par ? pr.sc : pr.sc2;
-    const int wslot = fused && par ? 2 : 0;
-    const int xqn = par ? 2 : 1;   // xq of a field that iterated before this launch (parity par ^ 1)
-    // fields that iterate before this launch's finish (uniform over the block)
-    const unsigned act0 = rhs_mask<NR>(pr, sin, rhs0, ST_ACTIVE);
-    double part[NR];
-#pragma unroll
-    for (int j = 0; j < NR; ++j) part[j] = 0.0;
-    const Geom g = pr.g;
-    const int np = MP ? g.S[2] * xy_kp(pr.sorder[KA]) : g.S[2];   // sites staged in LDS
-    FieldPtr fp{QR ? pr.r : pr.p, g.V, pr.nrhs}, fq{fused && par ? pr.p : pr.q, g.V, pr.nrhs};
-    // the fields of this launch's records that the finish's decision reads,
-    // loaded early by the thread that decides, so the staging covers the latency
-    Scal c0[NR];
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        c0[j] = Scal{};
-        if (fused && threadIdx.x == 0 && rhs0 + j < pr.nrhs) {
-            const Scal &m = sin[rhs0 + j];
-            c0[j].state = m.state;
-            c0[j].rho = m.rho;
-            c0[j].stop2 = m.stop2;
-            c0[j].iters = m.iters;
-            c0[j].since_ru = m.since_ru;
-            c0[j].beta = m.beta;
-            c0[j].restart = m.restart;
-            c0[j].xq = m.xq;
-        }
-    }
-    double as[NR][4], ar[NR][4];
-    if (fin && act0) {
-        col_issue<NR>(pr, rhs0, act0, as, par ? 0 : 2, pr.nsb[KA]);
-        col_issue<NR>(pr, rhs0, act0, ar, 1, pr.nsb[KB]);
-    }
-    auto reduce = [&]() {
-        if (fin && act0) {
-            col_reduce<NR>(pr, rhs0, act0, as, fsig, par ? 0 : 2, pr.nsb[KA]);
-            col_reduce<NR>(pr, rhs0, act0, ar, frho, 1, pr.nsb[KB]);
-        }
-    };
-    // the plane is staged for the fields active before the finish (a field
-    // that the finish freezes is staged for nothing, once per reliable update)
-    if (XY && act0) stage_plane<P, NR>(fp, rhs0, act0, s, g.V, xy, np, reduce);
-    else if (fin && act0) {
-        reduce();
-        __syncthreads();
-    }
-    // thread 0 applies the finish and shares the decision through LDS (one
-    // barrier); site block 0 of the group stores the records at the end
-    unsigned act = act0;
-    if (fused) {
-        if (threadIdx.x == 0)
-#pragma unroll
-            for (int j = 0; j < NR; ++j) {
-                const bool live = act0 >> j & 1;
-                if (fin) {
-                    const Fin f = cg_transition(pr, c0[j], live ? fsig[j] : 0.0, live ? frho[j] : 0.0, xqn);
-                    fact[j] = live && f.state == ST_ACTIVE;
-                    fbeta[j] = f.beta;
-                    frestart[j] = 0;
-                    foldq[j] = par ^ 1;
-                } else {
-                    fact[j] = live;
-                    fbeta[j] = c0[j].beta;
-                    frestart[j] = c0[j].restart;
-                    foldq[j] = c0[j].xq & 1;
-                }
-            }
-        __syncthreads();
-        act = 0;
-#pragma unroll
-        for (int j = 0; j < NR; ++j)
-            if (fact[j]) act |= 1u << j;
-    }
-    if (act && s < g.V) {
-        const void *U = R12 ? pr.U12 : pr.U_lo;
-        cx<R> acc[NR][12];
-        hopping<P, true, NR, ORD, XY, false, false, R12>(g, s, U, fp, rhs0, act, acc, nullptr, xy,
-                                                         s - (int)threadIdx.x, np);
-#pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            if (act >> j & 1) {
-                cx<R> self[12], o[12];
-                if constexpr (XY) LdsSpinor<P>::get(xy, np, j, threadIdx.x, self);
-                else Spinor<P>::load(fp, rhs0 + j, s, self);
-                wilson_finish<R>((R)pr.diag, self, acc[j], o);
-                if constexpr (QR) {
-                    if (!(fused ? frestart[j] : pr.sc[rhs0 + j].restart)) {
-                        const R b = (R)(fused ? fbeta[j] : pr.sc[rhs0 + j].beta);
-                        const FieldPtr fo{fused && foldq[j] ? pr.p : pr.q, g.V, pr.nrhs};
-                        cx<R> qo[12];
-                        Spinor<P>::template load<NT>(fo, rhs0 + j, s, qo);
-#pragma unroll
-                        for (int k = 0; k < 12; ++k) o[k] = {o[k].re + b * qo[k].re, o[k].im + b * qo[k].im};
-                    }
-                }
-                Spinor<P>::template store<NT>(fq, rhs0 + j, s, o);
-                double n = 0;
-#pragma unroll
-                for (int k = 0; k < 12; ++k) n += (double)norm2(o[k]);
-                part[j] = n;
-            }
-        }
-    }
-    if (act) {
-        block_sum<NR>(part);
-        if (threadIdx.x == 0)
-#pragma unroll
-            for (int j = 0; j < NR; ++j)
-                if (act >> j & 1) part_at(pr, sb, rhs0 + j, wslot) = part[j];
-    }
-    // the group's records after the finish (or copied unchanged in the chunk's
-    // first iteration), from the complete records read again
-    if (fused && sb == 0 && threadIdx.x == 0)
-#pragma unroll
-        for (int j = 0; j < NR; ++j)
-            if (rhs0 + j < pr.nrhs) {
-                const Scal full = sin[rhs0 + j];
-                if (fin) {
-                    const bool live = act0 >> j & 1;
-                    store_fin(sout[rhs0 + j], full,
-                              cg_transition(pr, full, live ? fsig[j] : 0.0, live ? frho[j] : 0.0, xqn));
-                } else {
-                    sout[rhs0 + j] = full;
-                }
-            }
-}
-
-// The finish functions run in one block; thread i updates the scalars of
-// right-hand side i.
-// Each reads its thread's scalar record before the partial sums, so the two
-// loads overlap (nrhs <= 64 < blockDim.x: one field per thread).
-__device__ __forceinline__ void phaseA_finish(const Prob &pr) {
-    __shared__ double sums[MAX_SUMS];
-    const int i = threadIdx.x;
-    Scal c0;
-    if (i < pr.nrhs) c0 = pr.sc[i];
-    if (!__syncthreads_or(i < pr.nrhs && c0.state == ST_ACTIVE)) {   // nothing to sum
-        if (i < pr.nrhs) pr.sc[i].pending_p = pr.sc[i].restart = 0;
-        return;
-    }
-    sum_all(pr, pr.nsb[KA], 1, sums);
-    if (i < pr.nrhs) {
-        Scal &c = pr.sc[i];
-        if (c0.state == ST_ACTIVE) {
-            const double sigma = sums[i];
-            c.sigma = sigma;
-            if (!finite_pos(sigma)) c.state = ST_BREAKDOWN;
-            else c.alpha = c0.rho / sigma;
-        }
-        c.pending_p = 0;
-        c.restart = 0;
-    }
-}
-
-// ------------------------------------------------------------------ phase B
-// Phase A's reduction inside the phase-B blocks (FA): each block sums phase
-// A's partials of its own fields, so alpha = rho / sigma is known without a
-// finish launch between the phases.  Wave w takes fields j = w, w + nw, ...
-// of the tile and adds exactly as sum_all does (same lanes, same order, same
-// butterfly), so every block gets the sigma the finish after phase B records.
-// fa_issue loads a lane's first four partials (before the plane staging, whose
-// latency then covers them); fa_reduce completes the sums into sig[j] (LDS,
-// read after the block's next barrier).
+// Partials of the tile's fields rhs0.. (those in act), slot `slot`, nsb site
+// blocks: wave w takes fields j = w, w + nw, ... and adds exactly as sum_all
+// does (same lanes, same order, same butterfly).  col_issue loads a lane's
+// first four partials, col_reduce completes the sums into out[j].
 template <int NR>
 __device__ __forceinline__ void col_issue(const Prob &pr, int rhs0, unsigned act, double (&a)[NR][4], int slot,
                                           int nsb) {
@@ -560,6 +356,260 @@ __device__ __forceinline__ void col_reduce(const Prob &pr, int rhs0, unsigned ac
     }
 }
 
+// The finish of the previous iteration inside phase A's blocks (see
+// phaseA_tile; the even-odd phase A too): begin issues the loads early, reduce
+// (before a barrier of the block) sums the partials, decide gives the fields
+// that iterate, in every thread, store writes the group's records.
+template <int NR> struct FinShared {
+    double sig[NR], rho[NR], beta[NR];
+    int act[NR], restart[NR], oldq[NR];   // oldq: the buffer of the old q (0: pr.q, 1: pr.p)
+};
+template <int NR> struct FusedFinish {
+    const Prob &pr;
+    FinShared<NR> &sh;
+    const int rhs0, par;
+    const bool fused, fin;   // uniform over the launch
+    const Scal *sin;
+    const int xqn;           // xq of a field that iterated before this launch (parity par ^ 1)
+    unsigned act0;           // fields that iterate before this launch's finish (uniform over the block)
+    Scal c0[NR];
+    double as[NR][4], ar[NR][4];
+
+    __device__ __forceinline__ FusedFinish(const Prob &p, FinShared<NR> &f, int r0, bool on, int pa, int first)
+        : pr(p), sh(f), rhs0(r0), par(pa), fused(on && pa >= 0), fin(on && pa >= 0 && !first),
+          sin(on && pa > 0 ? p.sc2 : p.sc), xqn(pa ? 2 : 1) {
+        act0 = rhs_mask<NR>(pr, sin, rhs0, ST_ACTIVE);
+    }
+    __device__ __forceinline__ void begin() {
+        // the fields of this launch's records that the finish's decision reads,
+        // loaded early by the thread that decides, so the staging covers the latency
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            c0[j] = Scal{};
+            if (fused && threadIdx.x == 0 && rhs0 + j < pr.nrhs) {
+                const Scal &m = sin[rhs0 + j];
+                c0[j].state = m.state;
+                c0[j].rho = m.rho;
+                c0[j].stop2 = m.stop2;
+                c0[j].iters = m.iters;
+                c0[j].since_ru = m.since_ru;
+                c0[j].beta = m.beta;
+                c0[j].restart = m.restart;
+                c0[j].xq = m.xq;
+            }
+        }
+        if (fin && act0) {
+            col_issue<NR>(pr, rhs0, act0, as, par ? 0 : 2, pr.nsb[KA]);
+            col_issue<NR>(pr, rhs0, act0, ar, 1, pr.nsb[KB]);
+        }
+    }
+    __device__ __forceinline__ void reduce() {
+        if (fin && act0) {
+            col_reduce<NR>(pr, rhs0, act0, as, sh.sig, par ? 0 : 2, pr.nsb[KA]);
+            col_reduce<NR>(pr, rhs0, act0, ar, sh.rho, 1, pr.nsb[KB]);
+        }
+    }
+    // thread 0 applies the finish and shares the decision through LDS (one barrier)
+    __device__ __forceinline__ unsigned decide() {
+        if (!fused) return act0;
+        if (threadIdx.x == 0)
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                const bool live = act0 >> j & 1;
+                if (fin) {
+                    const Fin f = cg_transition(pr, c0[j], live ? sh.sig[j] : 0.0, live ? sh.rho[j] : 0.0, xqn);
+                    sh.act[j] = live && f.state == ST_ACTIVE;
+                    sh.beta[j] = f.beta;
+                    sh.restart[j] = 0;
+                    sh.oldq[j] = par ^ 1;
+                } else {
+                    sh.act[j] = live;
+                    sh.beta[j] = c0[j].beta;
+                    sh.restart[j] = c0[j].restart;
+                    sh.oldq[j] = c0[j].xq & 1;
+                }
+            }
+        __syncthreads();
+        unsigned act = 0;
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+            if (sh.act[j]) act |= 1u << j;
+        return act;
+    }
+    __device__ __forceinline__ bool restart(int j) const {
+        return fused ? sh.restart[j] : pr.sc[rhs0 + j].restart;
+    }
+    __device__ __forceinline__ double beta(int j) const { return fused ? sh.beta[j] : pr.sc[rhs0 + j].beta; }
+    __device__ __forceinline__ void *oldq(int j) const {   // the same in every lane: a scalar choice
+        return fused && __builtin_amdgcn_readfirstlane(sh.oldq[j]) ? pr.p : pr.q;
+    }
+    // slot of phase A's partials, buffer of the new q
+    __device__ __forceinline__ int slot() const { return fused && par ? 2 : 0; }
+    __device__ __forceinline__ void *newq() const { return fused && par ? pr.p : pr.q; }
+    // the group's records after the finish (or copied unchanged in the chunk's
+    // first iteration), from the complete records read again: by site block 0
+    __device__ __forceinline__ void store(int sb) {
+        if (fused && sb == 0 && threadIdx.x == 0)
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (rhs0 + j < pr.nrhs) {
+                    Scal *sout = par ? pr.sc : pr.sc2;
+                    const Scal full = sin[rhs0 + j];
+                    if (fin) {
+                        const bool live = act0 >> j & 1;
+                        store_fin(sout[rhs0 + j], full,
+                                  cg_transition(pr, full, live ? sh.sig[j] : 0.0, live ? sh.rho[j] : 0.0, xqn));
+                    } else {
+                        sout[rhs0 + j] = full;
+                    }
+                }
+    }
+};
+
+// ------------------------------------------------------------------ phase A
+// q = D^dagger p for active rhs; partial |q|^2 (of the stored q)
+// XY: plane-blocked (one xy-plane per block, x/y neighbours from LDS).
+// MP (with XY): several z-adjacent planes per block (stencil_tile).  All z
+// neighbours still come from memory: reading the ones inside the block from
+// LDS (a branch per lane) took phases A and B from 77 to 95 VGPRs and 6 to 5
+// waves per SIMD.
+// R12: the links are the gauge's reconstruct-12 copy pr.U12 (two rows per link).
+// QR: the direction is carried as q alone.  Since p = r + beta p_old, its image
+// q = D^dagger p is D^dagger r + beta q_old: the stencil reads r and each site
+// adds beta times its own old q (q = D^dagger r after a restart), so neither p
+// nor a pass forming it (phase C) is needed.  Only the site's own q is read,
+// so q is updated in place.
+//
+// Fused finish (par >= 0, with QR): the launch also completes the finish of the
+// iteration before it, so an iteration is two launches.  Every block sums, for
+// its own fields and in the finish's fixed order, phase A's partials of the
+// previous iteration (slot 2 for par 0, slot 0 for par 1) and phase B's (slot
+// 1), and applies the same transition (cg_transition) to the records it reads
+// from pr.sc (par 0) or pr.sc2 (par 1); the site block 0 of each field group
+// writes the results to the other array, which no block of this launch reads.
+// So every block gets the same alpha, beta and state, bitwise equal to what
+// k_finish would have recorded.  first = 1 (the chunk's first iteration): the
+// records are final already (the reliable update or the trailing finish of the
+// chunk before wrote them) and are copied unchanged.  Partials go to slot 0
+// (par 0) or 2 (par 1).
+// With the fused finish q alternates between two buffers, pr.q (par 0) and
+// pr.p (par 1), so that phase B can add two iterations' alpha q to x_lo in one
+// pass (see phaseB_tile): the old q is read from the other buffer (in the
+// chunk's first iteration, from the one the field's record names).
+template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, bool NT = false, bool QR = false,
+          bool MP = false>
+__device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1, int first = 0) {
+    typedef typename real_of<P>::type R;
+    typedef typename LdsSpinor<P>::word W;
+    __shared__ W xy[XY ? NR * LdsWords<P>::value * (MP ? 512 : 256) : 1];
+    __shared__ FinShared<NR> fs;
+    int sb, grp, s;
+    stencil_tile<XY, MP>(pr, KA, t, sb, grp, s);
+    const int rhs0 = grp * NR;
+    FusedFinish<NR> ff(pr, fs, rhs0, QR, par, first);
+    const unsigned act0 = ff.act0;
+    double part[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) part[j] = 0.0;
+    const Geom g = pr.g;
+    const int np = MP ? g.S[2] * xy_kp(pr.sorder[KA]) : g.S[2];   // sites staged in LDS
+    FieldPtr fp{QR ? pr.r : pr.p, g.V, pr.nrhs}, fq{ff.newq(), g.V, pr.nrhs};
+    ff.begin();
+    // the plane is staged for the fields active before the finish (a field
+    // that the finish freezes is staged for nothing, once per reliable update)
+    if (XY && act0) stage_plane<P, NR>(fp, rhs0, act0, s, g.V, xy, np, [&]() { ff.reduce(); });
+    else if (ff.fin && act0) {
+        ff.reduce();
+        __syncthreads();
+    }
+    const unsigned act = ff.decide();
+    if (act && s < g.V) {
+        const void *U = R12 ? pr.U12 : pr.U_lo;
+        // FP64: whether there is a direction to add (not after a restart) is
+        // known before the hops; a branch on a load after them keeps the last
+        // hops' operands live (site blocks then spill at 3 waves per SIMD).
+        // FP32 phase A is 1 % faster with it after them.
+        bool keep[NR];
+        R beta[NR];
+        if constexpr (P == P64)
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                keep[j] = QR && (act >> j & 1) && !ff.restart(j);
+                beta[j] = keep[j] ? (R)ff.beta(j) : R(0);
+            }
+        cx<R> acc[NR][12];
+        hopping<P, true, NR, ORD, XY, false, false, R12>(g, s, U, fp, rhs0, act, acc, nullptr, xy,
+                                                         s - (int)threadIdx.x, np);
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            if (act >> j & 1) {
+                cx<R> self[12], o[12];
+                if constexpr (XY) LdsSpinor<P>::get(xy, np, j, threadIdx.x, self);
+                else Spinor<P>::load(fp, rhs0 + j, s, self);
+                wilson_finish<R>((R)pr.diag, self, acc[j], o);
+                if constexpr (QR) {
+                    if constexpr (P != P64) keep[j] = !ff.restart(j);
+                    if (keep[j]) {
+                        const R b = P == P64 ? beta[j] : (R)ff.beta(j);
+                        const FieldPtr fo{ff.oldq(j), g.V, pr.nrhs};
+                        cx<R> qo[12];
+                        Spinor<P>::template load<NT>(fo, rhs0 + j, s, qo);
+#pragma unroll
+                        for (int k = 0; k < 12; ++k) o[k] = {o[k].re + b * qo[k].re, o[k].im + b * qo[k].im};
+                    }
+                }
+                Spinor<P>::template store<NT>(fq, rhs0 + j, s, o);
+                double n = 0;
+#pragma unroll
+                for (int k = 0; k < 12; ++k) n += (double)norm2(o[k]);
+                part[j] = n;
+            }
+        }
+    }
+    if (act) {
+        block_sum<NR>(part);
+        if (threadIdx.x == 0)
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (act >> j & 1) part_at(pr, sb, rhs0 + j, ff.slot()) = part[j];
+    }
+    ff.store(sb);
+}
+
+// The finish functions run in one block; thread i updates the scalars of
+// right-hand side i.
+// Each reads its thread's scalar record before the partial sums, so the two
+// loads overlap (nrhs <= 64 < blockDim.x: one field per thread).
+__device__ __forceinline__ void phaseA_finish(const Prob &pr) {
+    __shared__ double sums[MAX_SUMS];
+    const int i = threadIdx.x;
+    Scal c0;
+    if (i < pr.nrhs) c0 = pr.sc[i];
+    if (!__syncthreads_or(i < pr.nrhs && c0.state == ST_ACTIVE)) {   // nothing to sum
+        if (i < pr.nrhs) pr.sc[i].pending_p = pr.sc[i].restart = 0;
+        return;
+    }
+    sum_all(pr, pr.nsb[KA], 1, sums);
+    if (i < pr.nrhs) {
+        Scal &c = pr.sc[i];
+        if (c0.state == ST_ACTIVE) {
+            const double sigma = sums[i];
+            c.sigma = sigma;
+            if (!finite_pos(sigma)) c.state = ST_BREAKDOWN;
+            else c.alpha = c0.rho / sigma;
+        }
+        c.pending_p = 0;
+        c.restart = 0;
+    }
+}
+
+// ------------------------------------------------------------------ phase B
+// Phase A's reduction inside the phase-B blocks (FA): each block sums phase
+// A's partials of its own fields, so alpha = rho / sigma is known without a
+// finish launch between the phases, and every block gets the sigma the finish
+// after phase B records.  fa_issue comes before the plane staging, whose
+// latency then covers its loads; fa_reduce completes the sums into sig[j] (LDS,
+// read after the block's next barrier).
 template <int NR>
 __device__ __forceinline__ void fa_issue(const Prob &pr, int rhs0, unsigned act, double (&a)[NR][4], int slot = 0) {
     col_issue<NR>(pr, rhs0, act, a, slot, pr.nsb[KA]);
@@ -588,8 +638,9 @@ __device__ __forceinline__ void fa_reduce(const Prob &pr, int rhs0, unsigned act
 // launch 70.1 -> 64.3 us, whole solves at 14^4 x 16 FP32 16.1 -> 15.5 ms, 12^4
 // x 12 FP64 14.0 -> 13.4 ms, 16^3 x 32 x 12 FP16N (whose x_lo is FP32) 35.1 ->
 // 33.2 ms; a single 8^4 field, bound by latency, 2.08 -> 2.10 ms.  last = 1
-// (the chunk's last iteration): parity 0 adds its own alpha q at once.  A field that freezes after a parity-0 iteration keeps
-// its pending alpha q (xq bit 1) for R1.
+// (the chunk's last iteration): parity 0 adds its own alpha q at once.  A
+// field that freezes after a parity-0 iteration keeps its pending alpha q (xq
+// bit 1) for R1.
 template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, bool NT = false, bool FA = false,
           bool MP = false>
 __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1, int last = 0) {

@@ -20,6 +20,8 @@
 // two sites 2k, 2k+1 have opposite parities).
 #pragma once
 
+#include <type_traits>
+
 #include "cg_core.h"
 
 namespace wd {
@@ -46,10 +48,14 @@ __device__ __forceinline__ void eo_tile(const Prob &pr, int K, int t, int &sb, i
 
 // XY: stage the half-plane of the hop's input field (the other parity's sites
 // on the block's xy-plane) in LDS; every thread of the block calls it.
-template <int P, int NR, bool XY>
+template <int P, int NR, bool XY, typename Hook = NoHook>
 __device__ __forceinline__ void eo_stage(const Prob &pr, const FieldPtr &in, int rhs0, unsigned act, int k,
-                                         typename LdsSpinor<P>::word *xy) {
-    if constexpr (XY) stage_plane<P, NR>(in, rhs0, act, k, pr.vf, xy, pr.g.S[2] >> 1);
+                                         typename LdsSpinor<P>::word *xy, Hook hook = {}) {
+    if constexpr (XY) stage_plane<P, NR>(in, rhs0, act, k, pr.vf, xy, pr.g.S[2] >> 1, hook);
+    else {
+        hook();
+        if constexpr (!std::is_same<Hook, NoHook>::value) __syncthreads();
+    }
 }
 
 // First half hop, onto the odd sites: tmp_o = H_oe v_e (H^dagger with DAG).
@@ -58,8 +64,13 @@ __device__ __forceinline__ void eo_stage(const Prob &pr, const FieldPtr &in, int
 // the second halves of phases A and B): links from the reconstruct-12 copy.
 // XY (here and there): half-plane blocks, the x and y neighbours from LDS, hop
 // order 5 (z and t first); one rhs per thread.
+// par >= 0: the fused finish (see phaseA_tile).  Phase A's first hop still sees
+// the records of before the finish that phase A's second hop applies (a field
+// that freezes there has been hopped for nothing, once per reliable update);
+// phase B's hops the records that phase A wrote, and q in the buffer of this
+// parity.
 template <int P, int NR, bool DAG, bool QR = false, bool R12 = false, bool XY = false>
-__device__ __forceinline__ void eo_hop1_tile(const Prob &pr, int t) {
+__device__ __forceinline__ void eo_hop1_tile(const Prob &pr, int t, int par = -1) {
     typedef typename real_of<P>::type R;
     typedef typename LdsSpinor<P>::word W;
     extern __shared__ uint4 eo_lds[];   // XY: the half-plane, sized at launch
@@ -68,9 +79,10 @@ __device__ __forceinline__ void eo_hop1_tile(const Prob &pr, int t) {
     int sb, grp, k;
     eo_tile<XY>(pr, K, t, sb, grp, k);
     const int rhs0 = grp * NR;
-    const unsigned act = rhs_mask<NR>(pr, rhs0, ST_ACTIVE);
+    const Scal *sc = par < 0 ? pr.sc : (DAG ? par > 0 : par == 0) ? pr.sc2 : pr.sc;
+    const unsigned act = rhs_mask<NR>(pr, sc, rhs0, ST_ACTIVE);
     if (!act) return;   // uniform over the block
-    FieldPtr fin{DAG ? (QR ? pr.r : pr.p) : pr.q, pr.vf, pr.nrhs}, fo{pr.tmp, pr.vf, pr.nrhs};
+    FieldPtr fin{DAG ? (QR ? pr.r : pr.p) : par > 0 ? pr.p : pr.q, pr.vf, pr.nrhs}, fo{pr.tmp, pr.vf, pr.nrhs};
     eo_stage<P, NR, XY>(pr, fin, rhs0, act, k, xy);
     if (k >= pr.vf) return;
     const Geom g = pr.g;
@@ -85,25 +97,30 @@ __device__ __forceinline__ void eo_hop1_tile(const Prob &pr, int t) {
 
 // Phase A, second half: q_e = A p_e - c H^dagger_eo tmp_o, partial |q|^2.
 // QR: with r in place of p, plus beta times the old q_e (not after a restart).
+// par, first: the fused finish of phaseA_tile (two launches less per
+// iteration: the finishes took 8.9 of 150 us at 14^4 x 16, FP32).
 template <int P, int NR, bool QR = false, bool R12 = false, bool XY = false>
-__device__ __forceinline__ void eo_phaseA_tile(const Prob &pr, int t) {
+__device__ __forceinline__ void eo_phaseA_tile(const Prob &pr, int t, int par = -1, int first = 0) {
     typedef typename real_of<P>::type R;
     typedef typename LdsSpinor<P>::word W;
     extern __shared__ uint4 eo_lds[];   // XY: the half-plane, sized at launch
     W *xy = (W *)eo_lds;
+    __shared__ FinShared<NR> fs;
     int sb, grp, k;
     eo_tile<XY>(pr, KA, t, sb, grp, k);
     const int rhs0 = grp * NR;
-    const unsigned act = rhs_mask<NR>(pr, rhs0, ST_ACTIVE);
+    FusedFinish<NR> ff(pr, fs, rhs0, QR, par, first);
     double part[NR];
 #pragma unroll
     for (int j = 0; j < NR; ++j) part[j] = 0.0;
     FieldPtr ft{pr.tmp, pr.vf, pr.nrhs};
-    if (act) eo_stage<P, NR, XY>(pr, ft, rhs0, act, k, xy);
+    ff.begin();
+    if (ff.act0) eo_stage<P, NR, XY>(pr, ft, rhs0, ff.act0, k, xy, [&]() { ff.reduce(); });
+    const unsigned act = ff.decide();
     if (act && k < pr.vf) {
         const Geom g = pr.g;
         const int s = eo_site(g, k, 0);
-        FieldPtr fp{QR ? pr.r : pr.p, pr.vf, pr.nrhs}, fq{pr.q, pr.vf, pr.nrhs};
+        FieldPtr fp{QR ? pr.r : pr.p, pr.vf, pr.nrhs}, fq{ff.newq(), pr.vf, pr.nrhs};
         cx<R> acc[NR][12];
         hopping<P, true, NR, XY ? 5 : 1, XY, true, false, R12>(g, s, R12 ? pr.U12 : pr.U_lo, ft, rhs0, act, acc,
                                                                nullptr, xy, k - (int)threadIdx.x, g.S[2] >> 1);
@@ -116,11 +133,11 @@ __device__ __forceinline__ void eo_phaseA_tile(const Prob &pr, int t) {
 #pragma unroll
                 for (int m = 0; m < 12; ++m) o[m] = {fma(-c, acc[j][m].re, a * v[m].re), fma(-c, acc[j][m].im, a * v[m].im)};
                 if constexpr (QR) {
-                    const Scal &sc = pr.sc[rhs0 + j];
-                    if (!sc.restart) {
-                        const R b = (R)sc.beta;
+                    if (!ff.restart(j)) {
+                        const R b = (R)ff.beta(j);
+                        const FieldPtr fo{ff.oldq(j), pr.vf, pr.nrhs};
                         cx<R> qo[12];
-                        Spinor<P>::load(fq, rhs0 + j, k, qo);
+                        Spinor<P>::load(fo, rhs0 + j, k, qo);
 #pragma unroll
                         for (int m = 0; m < 12; ++m) o[m] = {o[m].re + b * qo[m].re, o[m].im + b * qo[m].im};
                     }
@@ -138,33 +155,55 @@ __device__ __forceinline__ void eo_phaseA_tile(const Prob &pr, int t) {
         if (threadIdx.x == 0)
 #pragma unroll
             for (int j = 0; j < NR; ++j)
-                if (act >> j & 1) part_at(pr, sb, rhs0 + j, 0) = part[j];
+                if (act >> j & 1) part_at(pr, sb, rhs0 + j, ff.slot()) = part[j];
     }
+    ff.store(sb);
 }
 
 // Phase B, second half: t_e = A q_e - c H_eo tmp_o; r -= alpha t; x_lo += alpha q;
-// partial |r|^2
+// partial |r|^2.  par, last: as in phaseB_tile with FA (phase A's reduction
+// completed here, x_lo updated once per pair of iterations); par < 0: alpha is
+// in the record and x_lo updated at once.
 template <int P, int NR, bool R12 = false, bool XY = false>
-__device__ __forceinline__ void eo_phaseB_tile(const Prob &pr, int t) {
+__device__ __forceinline__ void eo_phaseB_tile(const Prob &pr, int t, int par = -1, int last = 0) {
     typedef typename real_of<P>::type R;
     constexpr int XP = XPrec<P>::value;
     typedef typename real_of<XP>::type RX;
     typedef typename LdsSpinor<P>::word W;
     extern __shared__ uint4 eo_lds[];   // XY: the half-plane, sized at launch
     W *xy = (W *)eo_lds;
+    __shared__ double sig[NR];
     int sb, grp, k;
     eo_tile<XY>(pr, KB, t, sb, grp, k);
     const int rhs0 = grp * NR;
-    const unsigned act = rhs_mask<NR>(pr, rhs0, ST_ACTIVE);
+    const bool fused = par >= 0;
+    const Scal *sc = par == 0 ? pr.sc2 : pr.sc;
+    const int aslot = par > 0 ? 2 : 0;
+    unsigned act = rhs_mask<NR>(pr, sc, rhs0, ST_ACTIVE);
     double part[NR];
 #pragma unroll
     for (int j = 0; j < NR; ++j) part[j] = 0.0;
+    const bool xup = par != 0 || last;   // this launch updates x_lo
     FieldPtr ft{pr.tmp, pr.vf, pr.nrhs};
-    if (act) eo_stage<P, NR, XY>(pr, ft, rhs0, act, k, xy);
+    if (act) {   // uniform over the block
+        double ps[NR][4];
+        if (fused) fa_issue<NR>(pr, rhs0, act, ps, aslot);
+        eo_stage<P, NR, XY>(pr, ft, rhs0, act, k, xy, [&]() {
+            if (fused) fa_reduce<NR>(pr, rhs0, act, ps, sig, aslot);
+        });
+        if (fused)
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if ((act >> j & 1) && !finite_pos(sig[j])) act &= ~(1u << j);
+    }
     if (act && k < pr.vf) {
         const Geom g = pr.g;
         const int s = eo_site(g, k, 0);
-        FieldPtr fq{pr.q, pr.vf, pr.nrhs}, fr{pr.r, pr.vf, pr.nrhs}, fx{pr.x_lo, pr.vf, pr.nrhs};
+        FieldPtr fq{par > 0 ? pr.p : pr.q, pr.vf, pr.nrhs}, fr{pr.r, pr.vf, pr.nrhs}, fx{pr.x_lo, pr.vf, pr.nrhs};
+        double ald[NR];   // before the hops: a branch after them would split their arithmetic
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+            ald[j] = !(act >> j & 1) ? 0.0 : fused ? sc[rhs0 + j].rho / sig[j] : sc[rhs0 + j].alpha;
         cx<R> acc[NR][12];
         hopping<P, false, NR, XY ? 5 : 1, XY, true, false, R12>(g, s, R12 ? pr.U12 : pr.U_lo, ft, rhs0, act, acc,
                                                                 nullptr, xy, k - (int)threadIdx.x, g.S[2] >> 1);
@@ -172,7 +211,7 @@ __device__ __forceinline__ void eo_phaseB_tile(const Prob &pr, int t) {
 #pragma unroll
         for (int j = 0; j < NR; ++j) {
             if (act >> j & 1) {
-                const R al = (R)pr.sc[rhs0 + j].alpha;
+                const R al = (R)ald[j];
                 cx<R> q[12], r[12];
                 Spinor<P>::load(fq, rhs0 + j, k, q);
                 Spinor<P>::load(fr, rhs0 + j, k, r);
@@ -186,12 +225,27 @@ __device__ __forceinline__ void eo_phaseB_tile(const Prob &pr, int t) {
 #pragma unroll
                 for (int m = 0; m < 12; ++m) n += (double)norm2(r[m]);
                 part[j] = n;
+                if (!xup) continue;
+                // issued once r is done with, q read again (as in phaseB_tile)
+                int kx = k;
+                asm volatile("" : "+v"(kx) : "v"(n));
                 cx<RX> x[12];
-                Spinor<XP>::load(fx, rhs0 + j, k, x);
-                const RX ax = (RX)pr.sc[rhs0 + j].alpha;
+                Spinor<XP>::load(fx, rhs0 + j, kx, x);
+                if (par > 0) {
+                    const FieldPtr fo{pr.q, pr.vf, pr.nrhs};
+                    const RX ao = (RX)sc[rhs0 + j].alpha;
+                    cx<R> qo[12];
+                    Spinor<P>::load(fo, rhs0 + j, kx, qo);
+#pragma unroll
+                    for (int m = 0; m < 12; ++m) x[m] = {x[m].re + ao * (RX)qo[m].re, x[m].im + ao * (RX)qo[m].im};
+                }
+                int kq = kx;
+                asm volatile("" : "+v"(kq) : "v"(x[0].re), "v"(x[11].im));
+                Spinor<P>::load(fq, rhs0 + j, kq, q);
+                const RX ax = (RX)ald[j];
 #pragma unroll
                 for (int m = 0; m < 12; ++m) x[m] = {x[m].re + ax * (RX)q[m].re, x[m].im + ax * (RX)q[m].im};
-                Spinor<XP>::store(fx, rhs0 + j, k, x);
+                Spinor<XP>::store(fx, rhs0 + j, kx, x);
             }
         }
     }
@@ -200,7 +254,7 @@ __device__ __forceinline__ void eo_phaseB_tile(const Prob &pr, int t) {
         if (threadIdx.x == 0)
 #pragma unroll
             for (int j = 0; j < NR; ++j)
-                if (act >> j & 1) part_at(pr, sb, rhs0 + j, 0) = part[j];
+                if (act >> j & 1) part_at(pr, sb, rhs0 + j, fused ? 1 : 0) = part[j];
     }
 }
 
@@ -223,8 +277,9 @@ __device__ __forceinline__ void eo_ru2a_tile(const Prob &pr, int t) {
 }
 
 // Reliable update, second half: r = b - (A x64 - c H_eo w_o) in FP64, stored
-// in the inner precision; partial |r|^2 in FP64 (frozen fields)
-template <int P, int NR>
+// in the inner precision; partial |r|^2 in FP64 (frozen fields).  ZX: x64 is
+// zero, so r = b without the hops (see ru2_tile).
+template <int P, int NR, bool ZX = false>
 __device__ __forceinline__ void eo_ru2b_tile(const Prob &pr, int t) {
     typedef typename real_of<P>::type R;
     int sb, grp, k;
@@ -240,19 +295,21 @@ __device__ __forceinline__ void eo_ru2b_tile(const Prob &pr, int t) {
         FieldPtr fw{pr.w64, pr.vf, pr.nrhs}, fx{pr.x64, pr.vf, pr.nrhs}, fb{pr.eta64, pr.vf, pr.nrhs},
             fr{pr.r, pr.vf, pr.nrhs};
         cx<double> acc[NR][12];
-        hopping<P64, false, NR, 1, false, true>(g, s, pr.U64, fw, rhs0, act, acc);
+        if constexpr (!ZX) hopping<P64, false, NR, 1, false, true>(g, s, pr.U64, fw, rhs0, act, acc);
 #pragma unroll
         for (int j = 0; j < NR; ++j) {
             if (act >> j & 1) {
                 cx<double> x[12], b[12];
-                Spinor<P64>::load(fx, rhs0 + j, k, x);
+                if constexpr (!ZX) Spinor<P64>::load(fx, rhs0 + j, k, x);
                 Spinor<P64>::load(fb, rhs0 + j, k, b);
                 cx<R> rl[12];
                 double n = 0;
 #pragma unroll
                 for (int m = 0; m < 12; ++m) {
-                    const cx<double> d = {b[m].re - (pr.diag * x[m].re - pr.eo_c * acc[j][m].re),
-                                          b[m].im - (pr.diag * x[m].im - pr.eo_c * acc[j][m].im)};
+                    cx<double> d = b[m];
+                    if constexpr (!ZX)
+                        d = {b[m].re - (pr.diag * x[m].re - pr.eo_c * acc[j][m].re),
+                             b[m].im - (pr.diag * x[m].im - pr.eo_c * acc[j][m].im)};
                     n += norm2(d);
                     rl[m] = {(R)d.re, (R)d.im};
                 }

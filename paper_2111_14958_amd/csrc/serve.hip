@@ -153,8 +153,8 @@ static LaunchSet server_launch(int inner, int eo, int xy, const int grid[NKIND])
     LaunchSet ls;
     ls.eo = eo;
     ls.qrec = 1;   // k_phaseA and the even-odd phase A carry the direction as q
-    ls.fused = !eo && !unfused_requested();   // site blocks, phase A's reduction in phase B: phase A
-                                              // finishes the iteration before it
+    ls.fused = !unfused_requested();   // phase A's reduction in phase B: phase A finishes the
+                                       // iteration before it
     for (int k = 0; k < NKIND; ++k) {
         const bool stencil = k == KA || k == KB || k == KR2 || k == KEA1 || k == KEB1 || k == KER2A;
         ls.k[k].block = blk;
@@ -245,10 +245,7 @@ static int init_slot(wd_server *s, Slot &sl) {
     launch_zero(w + L.xlo, spinor_bytes(inner == WD_F16N ? WD_F32 : inner, vf, rq.nrhs), st);
     const LaunchSet ls = single_launch(sl.prob, inner);
     launch_kind(KN, inner, ls, st, dp, 1);
-    if (eo) {
-        launch_eo_source(dp, vf, rq.nrhs, st);
-        launch_kind(KER2A, inner, ls, st, dp, 1);
-    }
+    if (eo) launch_eo_source(dp, vf, rq.nrhs, st);
     launch_first_residual(inner, ls, st, dp, 1, !rq.params.use_x0);
     launch_kind(KC, inner, ls, st, dp, 1);
     WD_HIP(hipGetLastError());
