@@ -132,8 +132,9 @@ int wd_unpack_spinor(const wd_gauge *g, int32_t prec, const void *in_dev, void *
  * Eq. (1) with the convention above; arithmetic in the precision `prec`
  * (WD_F16N: half storage with per-site norms, FP32 arithmetic).  With
  * WD_PACKED the buffers are in the packed layout of `prec`; otherwise they are
- * canonical complex128 and the call packs / unpacks through stream-ordered
- * temporary buffers.  The gauge handle must hold the links in `prec`.
+ * canonical complex128: read and written directly in FP64 and FP32 where
+ * Lx Ly <= 256 (and the launch shape is the default kind), else packed and
+ * unpacked through stream-ordered temporary buffers, with the same results.  The gauge handle must hold the links in `prec`.
  * in and out must not overlap.  Asynchronous on `stream`. */
 int wd_dslash(const wd_gauge *g, double m0, int32_t prec, const void *in_dev, void *out_dev,
               int32_t nrhs, uint32_t flags, void *stream);
@@ -145,7 +146,8 @@ int wd_dslash_dag(const wd_gauge *g, double m0, int32_t prec, const void *in_dev
  * or wd_dslash_dag (dagger = 1) on canonical complex128 in/out, with the packed
  * temporaries kept in a static device array of WD_NOALLOC_SCRATCH_BYTES that
  * the library holds on every device it runs on until the process ends, instead
- * of buffers allocated per call.  The call allocates nothing.  Both packed
+ * of buffers allocated per call (a call that reads and writes the canonical
+ * fields directly leaves it alone).  The call allocates nothing.  Both packed
  * fields (each rounded up to 256 bytes) must fit the array: 2 * nrhs * V *
  * (192 | 96 | 52) bytes for FP64 | FP32 | FP16N, else WD_ETOOBIG.  Every call on
  * one device shares that device's array, so calls that overlap on one device

@@ -128,6 +128,38 @@ __global__ __launch_bounds__(MP ? 512 : 256) void k_dslash_xy(Geom g, double dia
     }
 }
 
+// Plane-blocked variant on canonical complex128 fields, FP64 and FP32 arithmetic
+// (one plane, one rhs, hop order 5): without the launches that pack the input
+// and unpack the output, the packed copies' traffic (4 of 6 passes over a field)
+// and the two allocations of a call.  The same arithmetic per site as pack,
+// k_dslash_xy, unpack.  A lane's loads of a site are 192 bytes apart, a line per
+// lane (about 12 us of address processing at 14^4 x 16 per pass, 5 passes), which
+// is still less than the passes it replaces at every size: pack + operator +
+// unpack against this kernel 13x11x9x10 x 5 fields FP64 41 -> 18 us, FP32 42 ->
+// 15 us; 14^4 x 16 219 -> 123 us, 143 -> 109 us; 4^4 x 1 37 -> 8 us.  (A packed
+// input with a canonical output: 30, 27; 162, 111; 29 us.)
+template <int P, bool DAG, bool R12>
+__global__ __launch_bounds__(256) void k_dslash_cn(Geom g, double diag, const void *__restrict__ U, FieldPtr in,
+                                                   FieldPtr out, int remap, int order) {
+    typedef typename real_of<P>::type R;
+    typedef typename LdsSpinor<P>::word W;
+    extern __shared__ uint4 lds_raw[];
+    W *xy = (W *)lds_raw;
+    const int np = (int)blockDim.x;
+    const int b = remap ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int pl = b / in.nrhs, rhs = b - pl * in.nrhs;
+    const int s = order_site(g, order & 0xffff, pl * np + (int)threadIdx.x);
+    cx<R> self[12], acc[1][12], o[12];
+    CanonSpinor<P>::load(in, rhs, s, self);
+    LdsSpinor<P>::put(xy, np, 0, threadIdx.x, self);
+    __syncthreads();
+    hopping<P, DAG, 1, 5, true, false, false, R12, false, true>(g, s, U, in, rhs, 1u, acc, nullptr, xy,
+                                                                s - (int)threadIdx.x, np);
+    LdsSpinor<P>::get(xy, np, 0, threadIdx.x, self);
+    wilson_finish<R>((R)diag, self, acc[0], o);
+    CanonSpinor<P>::store(out, rhs, s, o);
+}
+
 // z-marching variant: a block walks a column of xy-planes along z (one rhs,
 // one t, the planes of z-chunk c), so every spinor is read from memory about
 // once by its own block instead of once per neighbouring plane.  Per plane:
@@ -375,7 +407,36 @@ int launch_dslash(const wd_gauge *gg, double m0, int prec, bool dag, const void 
     return WD_OK;
 }
 
-// Device memory of wd_dslash_noalloc: the packed input and output of one call.
+// Does the operator on canonical fields run on k_dslash_cn?  FP64 and FP32 where
+// the shape in force is the plane-blocked one with hop order 5 (the default, for
+// planes of up to 256 sites).  FP16N would quantise every neighbour again, and a
+// shape set or tuned to another kernel keeps it.
+static bool canonical_direct(const wd_gauge *gg, int prec, const Shape &sh) {
+    return prec != WD_F16N && sh.xylds == 1 && sh.ordered == 5 && sh.nr == 1 && sh.occ == 0 && sh.gmajor == 0 &&
+           gg->dims[0] * gg->dims[1] <= 256 && gg->V <= 0xffffffffll / 192;   // 32-bit byte offsets
+}
+
+static int launch_dslash_cn(const wd_gauge *gg, double m0, int prec, bool dag, const void *in, void *out, int nrhs,
+                            const Shape &sh, hipStream_t st) {
+    const Geom g = make_geom(gg);
+    const int np = g.S[2], strip = (sh.strip > 0 && sh.strip < g.L[2]) ? sh.strip : 0;
+    const bool r12 = prec == WD_F32 && gg->U12[WD_F32] != nullptr;
+    const void *U = r12 ? gg->U12[WD_F32] : gg->U[prec];
+    const FieldPtr fi{(void *)in, g.V, nrhs}, fo{out, g.V, nrhs};
+    const dim3 grid((unsigned)(g.L[2] * g.L[3] * nrhs)), block(np);
+    const size_t lds = xy_lds_bytes(prec, 1, np);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, lds, st, g, 4.0 + m0, U, fi, fo, sh.remap, strip);
+    };
+    if (prec == WD_F64) dag ? go(k_dslash_cn<P64, true, false>) : go(k_dslash_cn<P64, false, false>);
+    else if (r12) dag ? go(k_dslash_cn<P32, true, true>) : go(k_dslash_cn<P32, false, true>);
+    else dag ? go(k_dslash_cn<P32, true, false>) : go(k_dslash_cn<P32, false, false>);
+    WD_HIP(hipGetLastError());
+    return WD_OK;
+}
+
+// Device memory of wd_dslash_noalloc: the packed input and output of one call
+// (calls that run on k_dslash_cn do not use it, but are held to its size too).
 // Host code never passes the name itself to a kernel (on the host it is a
 // stand-in, not a device address); it uses the address hipGetSymbolAddress
 // returns for the current device, taken once per device.
@@ -420,7 +481,8 @@ static int dslash_entry(const wd_gauge *g, double m0, int32_t prec, const void *
     const Shape sh = shape_lookup(key);
     if (flags & WD_PACKED) return launch_dslash(g, m0, prec, dag, in, out, nrhs, sh, st);
 
-    // canonical complex128 in/out: pack, apply, unpack through temporaries
+    // canonical complex128 in/out: directly, or pack, apply, unpack through temporaries
+    const bool direct = canonical_direct(g, prec, sh);
     const size_t nb = spinor_bytes(prec, g->V, nrhs);
     if (noalloc) {
         // the two packed buffers, each at a 256-byte boundary, in the static scratch
@@ -428,6 +490,7 @@ static int dslash_entry(const wd_gauge *g, double m0, int32_t prec, const void *
         WD_CHECK(2 * nba <= (size_t)WD_NOALLOC_SCRATCH_BYTES, WD_ETOOBIG,
                  "%d fields of %lld sites in precision %d need %zu bytes of scratch, the static scratch holds %zu",
                  nrhs, (long long)g->V, prec, 2 * nba, (size_t)WD_NOALLOC_SCRATCH_BYTES);
+        if (direct) return launch_dslash_cn(g, m0, prec, dag, in, out, nrhs, sh, st);
         unsigned char *sp = nullptr;
         rc = scratch_ptr(&sp);
         if (rc) return rc;
@@ -436,6 +499,7 @@ static int dslash_entry(const wd_gauge *g, double m0, int32_t prec, const void *
         if (!rc) rc = launch_unpack_spinor(prec, sp + nba, out, (int)g->V, nrhs, st);
         return rc;
     }
+    if (direct) return launch_dslash_cn(g, m0, prec, dag, in, out, nrhs, sh, st);
     void *a = nullptr, *b = nullptr;
     WD_HIP(hipMallocAsync(&a, nb, st));
     hipError_t e = hipMallocAsync(&b, nb, st);

@@ -262,6 +262,26 @@ template <> struct Spinor<P16> {
     }
 };
 
+// Site s of field r of a canonical complex128 field [rhs][V][12], rounded to the
+// arithmetic of P (as packing does).  A lane's 192 bytes are contiguous, so a
+// wavefront's twelve loads touch the same 64 x 192 bytes, each a line per lane.
+template <int P> struct CanonSpinor {
+    typedef typename real_of<P>::type R;
+    __device__ static __forceinline__ void load(const FieldPtr &f, int r, int s, cx<R> o[12]) {
+        const gptr<const d2v> p = at<d2v>((const void *)f.p, (size_t)r * f.V * 192, (uint32_t)s * 192u);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            const d2v v = p[k];
+            o[k] = {(R)v.x, (R)v.y};
+        }
+    }
+    __device__ static __forceinline__ void store(const FieldPtr &f, int r, int s, const cx<R> o[12]) {
+        const gptr<d2v> p = at<d2v>(f.p, (size_t)r * f.V * 192, (uint32_t)s * 192u);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) p[k] = d2v{(double)o[k].re, (double)o[k].im};
+    }
+};
+
 // --------------------------------------------------------------- link views
 // Link<P>::load<R12>(U, g, mu, s, last_t, u): the link U_mu at site s.  last_t:
 // s is on the last time slice and mu = t, so the stored link carries the
@@ -485,6 +505,7 @@ template <> struct LdsSpinor<P64> {
 // (even-odd preconditioning; needs an even Lx); with XYLDS, plane0 and np
 // count half indices (the block's half-plane).
 // R12: U is a reconstruct-12 copy (two rows per link, FP32/FP16).
+// CN: `in` is a canonical complex128 field.
 // ZIN (with XYLDS; a block of several z-adjacent xy-planes, whose sites are
 // consecutive, all staged in `xy`): a z neighbour that lies in the block's
 // planes is read from LDS, the others from memory.
@@ -494,7 +515,7 @@ template <> struct LdsSpinor<P64> {
 // on entry, and on return `carry` holds the backward z hop of site s + z,
 // (1 + SB gamma_z) U_z(s)^dag psi(s), made from the link the forward z hop loads.
 template <int P, bool DAG, int NR, int ORDERED = 1, bool XYLDS = false, bool HALF = false, bool ZM = false,
-          bool R12 = false, bool ZIN = false>
+          bool R12 = false, bool ZIN = false, bool CN = false>
 __device__ __forceinline__ void hopping(const Geom &g, int s, const void *U, const FieldPtr &in,
                                         int rhs0, unsigned act, cx<typename real_of<P>::type> acc[NR][12],
                                         const cx<typename real_of<P>::type> (*first)[12] = nullptr,
@@ -582,7 +603,8 @@ __device__ __forceinline__ void hopping(const Geom &g, int s, const void *U, con
                     const int li = nb - plane0;   // in the block's planes: only one wave can diverge
                     if ((unsigned)li < (unsigned)np) LdsSpinor<P>::get(xy, np, j, li, p);
                     else Spinor<P>::load(in, rhs0 + j, nb, p);
-                } else Spinor<P>::load(in, rhs0 + j, HALF ? nb >> 1 : nb, p);
+                } else if constexpr (CN) CanonSpinor<P>::load(in, rhs0 + j, nb, p);
+                else Spinor<P>::load(in, rhs0 + j, HALF ? nb >> 1 : nb, p);
                 project<MU, S>(p, h);
                 if constexpr (FWD) link_mul(u, h, w);
                 else link_adj_mul(u, h, w);
