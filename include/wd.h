@@ -191,7 +191,7 @@ typedef struct {
                                chunk with grid barriers, -1: library default             */
     int32_t chunk;          /* CG iterations per graph replay (the host checks for
                                convergence between replays).  0 = library default:
-                               reliable_every (or 50), and for CG a replay cut
+                               reliable_every (or 50), and a replay cut
                                short, in multiples of 8, once the fields' decrease of
                                |r|^2 says they need fewer; the results do not depend
                                on the replay lengths                                  */

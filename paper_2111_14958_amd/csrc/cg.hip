@@ -11,8 +11,9 @@
 // and replays the chunk graph until no right-hand side is active, reading back
 // the summary (active count, abort flag, estimated iterations left) after each
 // replay; with the library's chunk length a replay is cut to that estimate.
-// BiCGSTAB (bicgstab_core.h) uses the same driver with the chunk
-// K x [S1, S2, S3, S4, S5], then R1, R2, summary.
+// BiCGSTAB (bicgstab_core.h) uses the same driver with the chunk S1, K x [F2,
+// S3, F4, F5], trailing finish (without room for the fused iteration's records:
+// K x [S1, S2, S3, S4, S5] with their finishes), then R1, R2, summary.
 #include <stdlib.h>
 #include <string.h>
 
@@ -206,7 +207,8 @@ void launch_eo_merge(const Prob *d, int64_t vf, int nrhs, void *sol, hipStream_t
 // run with the fused finish (K iterations, parity K & 1): the records that
 // iteration's phase A wrote (pr.sc2 for an odd K, else pr.sc) and its phase A
 // partials (slot 0 for an odd K, else slot 2) give the final records in pr.sc.
-constexpr int FIN_AB = 0x100, FIN_TRAIL = 0x200;
+// KS5 | FIN_TRAIL_BI: the trailing finish of a chunk of fused BiCGSTAB iterations.
+constexpr int FIN_AB = 0x100, FIN_TRAIL = 0x200, FIN_TRAIL_BI = 0x400;
 __global__ __launch_bounds__(1024) void k_finish(const Prob *__restrict__ probs, int nprob, int kind) {
     for (int j = 0; j < nprob; ++j) {
         const Prob &pr = probs[j];
@@ -224,6 +226,7 @@ __global__ __launch_bounds__(1024) void k_finish(const Prob *__restrict__ probs,
         case KS2: bi2_finish(pr); break;
         case KS4: bi4_finish(pr); break;
         case KS5: bi5_finish(pr); break;
+        case KS5 | FIN_TRAIL_BI: bi_trail_finish(pr); break;
         default: break;
         }
     }
@@ -231,10 +234,10 @@ __global__ __launch_bounds__(1024) void k_finish(const Prob *__restrict__ probs,
 
 // out[0] = right-hand sides still active or frozen over all problems,
 // out[1] = the persistent kernel's abort flag (0 when there is none),
-// out[2] = for one CG problem, an estimate of the iterations its active fields
+// out[2] = for one problem, an estimate of the iterations its active fields
 // still need: |r|^2 of each is extrapolated at its rate of decrease since the
 // previous summary (log-linear) down to the stopping value; -1 when unknown
-// (another method, several problems, a field without such a history).  The
+// (several problems, a field without such a history).  The
 // previous summary's |r|^2 and iteration count of each field sit 256 bytes
 // after out (SumHist; the summary area has room for MAX_RHS of them) and are
 // replaced.  One block of MAX_RHS threads.
@@ -254,11 +257,11 @@ __global__ void k_summary(const Prob *__restrict__ probs, int nprob, int *out, c
             }
         out[0] = live;
         out[1] = abort_flag ? *abort_flag : 0;
-        unknown = nprob != 1 || probs[0].method != METHOD_CGNE;
+        unknown = nprob != 1;
         need = 0;
     }
     __syncthreads();
-    if (nprob == 1 && probs[0].method == METHOD_CGNE && i < probs[0].nrhs) {
+    if (nprob == 1 && i < probs[0].nrhs) {
         const Scal &c = probs[0].sc[i];
         SumHist *h = (SumHist *)((char *)out + 256) + i;
         const SumHist prev = *h;
@@ -286,17 +289,24 @@ __global__ __launch_bounds__(256) void k_bi1(const Prob *__restrict__ probs, int
     bi1_tile<P>(pr, t_);
 }
 
-template <int P, int NR, bool S4, int ORD = 1, bool XY = false, bool R12 = false>
-__global__ __launch_bounds__(256) void k_bi_stencil(const Prob *__restrict__ probs, int nprob, int remap) {
+// F: the kernels of the fused iteration (F2, S3, F4, F5)
+template <int P, int NR, bool S4, int ORD = 1, bool XY = false, bool R12 = false, bool F = false>
+__global__ __launch_bounds__(256) void k_bi_stencil(const Prob *__restrict__ probs, int nprob, int remap, int first) {
     constexpr int K = S4 ? KS4 : KS2;
     WD_KERNEL_PROLOGUE(K)
-    bi_stencil_tile<P, NR, S4, ORD, XY, R12>(pr, t_);
+    bi_stencil_tile<P, NR, S4, ORD, XY, R12, F>(pr, t_, first);
+}
+
+template <int P, bool F = false>
+__global__ __launch_bounds__(256) void k_bi3(const Prob *__restrict__ probs, int nprob, int remap) {
+    WD_KERNEL_PROLOGUE(KS3)
+    bi3_tile<P, F>(pr, t_);
 }
 
 template <int P>
-__global__ __launch_bounds__(256) void k_bi3(const Prob *__restrict__ probs, int nprob, int remap) {
-    WD_KERNEL_PROLOGUE(KS3)
-    bi3_tile<P>(pr, t_);
+__global__ __launch_bounds__(256) void k_bi5f(const Prob *__restrict__ probs, int nprob, int remap) {
+    WD_KERNEL_PROLOGUE(KS5)
+    bi5f_tile<P>(pr, t_);
 }
 
 template <int P>
@@ -463,27 +473,42 @@ static void launch_R2(int nr, int xy, int grid, int blk, hipStream_t st, const P
 
 // plane blocks (xy): hop order 5, one rhs per thread, the reconstruct-12
 // links in FP32 when the gauge has them
-template <int P, bool S4>
-static void launch_BS(int nr, int xy, int r12, int grid, int blk, hipStream_t st, const Prob *d, int n, int remap) {
-    if (xy) {
+template <int P, bool S4, bool F>
+static void launch_BS(const KindShape &k, hipStream_t st, const Prob *d, int n, int first) {
+    const dim3 gr(k.grid), bl(k.block);
+    if (k.xy) {
         if constexpr (P == P32)
-            if (r12) {
-                hipLaunchKernelGGL((k_bi_stencil<P, 1, S4, 5, true, true>), dim3(grid), dim3(blk), 0, st, d, n, remap);
+            if (k.r12) {
+                hipLaunchKernelGGL((k_bi_stencil<P, 1, S4, 5, true, true, F>), gr, bl, 0, st, d, n, k.remap, first);
                 return;
             }
-        hipLaunchKernelGGL((k_bi_stencil<P, 1, S4, 5, true>), dim3(grid), dim3(blk), 0, st, d, n, remap);
-    } else if (nr == 1) hipLaunchKernelGGL((k_bi_stencil<P, 1, S4>), dim3(grid), dim3(blk), 0, st, d, n, remap);
-    else if (nr == 2) hipLaunchKernelGGL((k_bi_stencil<P, 2, S4>), dim3(grid), dim3(blk), 0, st, d, n, remap);
-    else hipLaunchKernelGGL((k_bi_stencil<P, 4, S4>), dim3(grid), dim3(blk), 0, st, d, n, remap);
+        hipLaunchKernelGGL((k_bi_stencil<P, 1, S4, 5, true, false, F>), gr, bl, 0, st, d, n, k.remap, first);
+    } else if (k.nr == 1) hipLaunchKernelGGL((k_bi_stencil<P, 1, S4, 1, false, false, F>), gr, bl, 0, st, d, n, k.remap, first);
+    else if (k.nr == 2) hipLaunchKernelGGL((k_bi_stencil<P, 2, S4, 1, false, false, F>), gr, bl, 0, st, d, n, k.remap, first);
+    else hipLaunchKernelGGL((k_bi_stencil<P, 4, S4, 1, false, false, F>), gr, bl, 0, st, d, n, k.remap, first);
 }
+// fused: the fused iteration's kernels (first: a chunk's first iteration)
 template <int P>
-static void launch_bicg(int kind, const KindShape &k, hipStream_t st, const Prob *d, int n) {
+static void launch_bicg(int kind, const KindShape &k, hipStream_t st, const Prob *d, int n, int fused, int first) {
+    const dim3 gr(k.grid), bl(k.block);
     switch (kind) {
-    case KS1: hipLaunchKernelGGL(k_bi1<P>, dim3(k.grid), dim3(k.block), 0, st, d, n, 0); break;
-    case KS2: launch_BS<P, false>(k.nr, k.xy, k.r12, k.grid, k.block, st, d, n, k.remap); break;
-    case KS3: hipLaunchKernelGGL(k_bi3<P>, dim3(k.grid), dim3(k.block), 0, st, d, n, 0); break;
-    case KS4: launch_BS<P, true>(k.nr, k.xy, k.r12, k.grid, k.block, st, d, n, k.remap); break;
-    case KS5: hipLaunchKernelGGL(k_bi5<P>, dim3(k.grid), dim3(k.block), 0, st, d, n, 0); break;
+    case KS1: hipLaunchKernelGGL(k_bi1<P>, gr, bl, 0, st, d, n, 0); break;
+    case KS2:
+        if (fused) launch_BS<P, false, true>(k, st, d, n, first);
+        else launch_BS<P, false, false>(k, st, d, n, 0);
+        break;
+    case KS3:
+        if (fused) hipLaunchKernelGGL((k_bi3<P, true>), gr, bl, 0, st, d, n, 0);
+        else hipLaunchKernelGGL((k_bi3<P, false>), gr, bl, 0, st, d, n, 0);
+        break;
+    case KS4:
+        if (fused) launch_BS<P, true, true>(k, st, d, n, 0);
+        else launch_BS<P, true, false>(k, st, d, n, 0);
+        break;
+    case KS5:
+        if (fused) hipLaunchKernelGGL(k_bi5f<P>, gr, bl, 0, st, d, n, 0);
+        else hipLaunchKernelGGL(k_bi5<P>, gr, bl, 0, st, d, n, 0);
+        break;
     }
 }
 
@@ -557,7 +582,7 @@ void launch_kind(int kind, int inner, const LaunchSet &ls, hipStream_t st, const
     }
     // with the fused finish, phase A finishes the previous iteration and a
     // trailing finish the chunk's last (launch_iterations)
-    if (reduces && !(par >= 0 && (kind == KA || kind == KB))) launch_finish_after(kind, ls, st, d, nprob);
+    if (reduces && !(par >= 0 && kind != KR2 && kind != KN)) launch_finish_after(kind, ls, st, d, nprob);
 }
 
 // The first true residual of a solve (R2).  x_zero: x64 is zero (no initial
@@ -641,9 +666,9 @@ static void launch_kind_tiles(int kind, int inner, const KindShape &k, hipStream
         hipLaunchKernelGGL(k_norm, dim3(k.grid), dim3(k.block), 0, st, d, nprob, 0);
         break;
     case KS1: case KS2: case KS3: case KS4: case KS5:
-        if (inner == P64) launch_bicg<P64>(kind, k, st, d, nprob);
-        else if (inner == P32) launch_bicg<P32>(kind, k, st, d, nprob);
-        else launch_bicg<P16>(kind, k, st, d, nprob);
+        if (inner == P64) launch_bicg<P64>(kind, k, st, d, nprob, par >= 0, first);
+        else if (inner == P32) launch_bicg<P32>(kind, k, st, d, nprob, par >= 0, first);
+        else launch_bicg<P16>(kind, k, st, d, nprob, par >= 0, first);
         break;
     }
 }
@@ -690,6 +715,12 @@ WsLayout ws_layout(int64_t V, int nrhs, int inner, int method, int eo) {
         L.rh = o; o += al256(spinor_bytes(inner, V, nrhs));
         L.sv = o; o += al256(spinor_bytes(inner, V, nrhs));
         L.tv = o; o += al256(spinor_bytes(inner, V, nrhs));
+    }
+    L.least = o;
+    L.bi_part2 = L.bi_rec = 0;
+    if (method == METHOD_BICGSTAB) {
+        L.bi_part2 = o; o += al256((size_t)((V + 63) / 64) * nrhs * BI_NP2 * sizeof(double));
+        L.bi_rec = o; o += al256(3 * sizeof(BiRec) * nrhs);
     }
     L.total = o;
     return L;
@@ -899,6 +930,10 @@ void fill_prob(Prob &pr, const wd_gauge *g, double m0, int nrhs, const wd_cg_par
     pr.sv = L.sv ? ws + L.sv : nullptr;
     pr.tv = L.tv ? ws + L.tv : nullptr;
     pr.bs = L.bscal ? (BScal *)(ws + L.bscal) : nullptr;
+    pr.part2 = L.bi_part2 ? (double *)(ws + L.bi_part2) : nullptr;
+    pr.rec2 = L.bi_rec ? (BiRec *)(ws + L.bi_rec) : nullptr;
+    pr.rec3 = pr.rec2 ? pr.rec2 + nrhs : nullptr;
+    pr.recm = pr.rec2 ? pr.rec3 + nrhs : nullptr;
     pr.eta_o = L.eta_o ? ws + L.eta_o : nullptr;
     pr.tmp = L.tmp ? ws + L.tmp : nullptr;
     pr.w64 = L.w64 ? ws + L.w64 : nullptr;
@@ -1106,7 +1141,7 @@ int cg_run(const wd_gauge *g, double m0, const void *src, void *sol, int nrhs, c
     const int64_t V = g->V;
     const int eo = p.precondition == WD_PRECOND_EO ? 1 : 0;
     const WsLayout L = ws_layout(V, nrhs, p.inner, p.method, eo);
-    WD_CHECK(ws_bytes >= L.total, WD_ENOMEM, "workspace of %zu bytes, %zu needed", ws_bytes, L.total);
+    WD_CHECK(ws_bytes >= L.least, WD_ENOMEM, "workspace of %zu bytes, %zu needed", ws_bytes, L.least);
     char *w = (char *)ws;
     Prob hp;
     memset(&hp, 0, sizeof(hp));
@@ -1118,6 +1153,8 @@ int cg_run(const wd_gauge *g, double m0, const void *src, void *sol, int nrhs, c
 
     const int K = p.chunk > 0 ? p.chunk : (p.reliable_every > 0 ? p.reliable_every : 50);
     const bool bicg = p.method == METHOD_BICGSTAB;
+    // the fused iteration needs the pieces after L.least
+    ls.bi_fused = bicg && ws_bytes >= L.total && !unfused_requested();
     const int persistent = (p.persistent == 1 && !bicg) ? 1 : 0;
     if (persistent) plan_persistent(ls, hp, V, nrhs, p.inner, p.max_cus);
     for (int k = 0; k < NKIND; ++k)   // kernels launched one by one are compiled for <= 256 threads
@@ -1177,7 +1214,7 @@ int cg_run(const wd_gauge *g, double m0, const void *src, void *sol, int nrhs, c
     key.inner = p.inner;
     key.persistent = persistent;
     key.max_cus = p.max_cus;
-    key.method = p.method | (eo << 4) | (ls.fused << 5);
+    key.method = p.method | (eo << 4) | (ls.fused << 5) | (ls.bi_fused << 6);
     for (int k = 0; k < NKIND; ++k) key.shp[k] = ls.k[k];
     // the graph of a chunk of Kc iterations (cached per length)
     auto chunk_graph = [&](int Kc, hipGraphExec_t *exec) -> int {
@@ -1185,8 +1222,15 @@ int cg_run(const wd_gauge *g, double m0, const void *src, void *sol, int nrhs, c
         int rec_rc = WD_OK;
         const int r = get_graph(key, [&](hipStream_t cs) {
             if (bicg) {
-                for (int it = 0; it < Kc; ++it)
-                    for (int k = KS1; k <= KS5; ++k) launch_kind(k, p.inner, ls, cs, dprob, 1);
+                if (ls.bi_fused) {
+                    launch_kind(KS1, p.inner, ls, cs, dprob, 1);   // fields that restart
+                    for (int it = 0; it < Kc; ++it)
+                        for (int k = KS2; k <= KS5; ++k) launch_kind(k, p.inner, ls, cs, dprob, 1, 0, it == 0);
+                    launch_finish(KS5 | FIN_TRAIL_BI, cs, dprob, 1);
+                } else {
+                    for (int it = 0; it < Kc; ++it)
+                        for (int k = KS1; k <= KS5; ++k) launch_kind(k, p.inner, ls, cs, dprob, 1);
+                }
                 launch_kind(KR1, p.inner, ls, cs, dprob, 1);
                 launch_kind(KR2, p.inner, ls, cs, dprob, 1);
                 launch_summary(cs, dprob, 1, dsum, dabort);

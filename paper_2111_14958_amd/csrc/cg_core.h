@@ -67,6 +67,8 @@ struct alignas(16) BScal {
     double pad;
 };
 
+struct BiRec;   // BiCGSTAB's records (bicgstab_core.h)
+
 struct alignas(16) Prob {
     Geom g;
     double diag;      // 4 + m0
@@ -94,6 +96,8 @@ struct alignas(16) Prob {
                               // launches of a chunk read one and write the other (iteration parity)
     void *rh, *v, *sv, *tv;   // BiCGSTAB: shadow residual r_hat, v = D p, s, t = D s
     BScal *bs;                // BiCGSTAB scalars [nrhs]
+    double *part2;            // BiCGSTAB, fused iteration: F4's partials, columns as in part
+    BiRec *rec2, *rec3, *recm;   // ... and its records [nrhs] after F2, S3 and F5
     void *eta_o;              // even-odd: odd half of the source (FP64)
     void *tmp;                // even-odd: odd-site intermediate of A and B (inner precision)
     void *w64;                // even-odd: odd-site intermediate of R2 (FP64)

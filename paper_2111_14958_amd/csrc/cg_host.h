@@ -24,6 +24,7 @@ struct LaunchSet {
     KindShape k[NKIND];
     int eo = 0;   // even-odd preconditioned solve: A, B, R2 are Schur kernels
     int qrec = 0; // phase A forms the direction q = D^dagger r + beta q (Dhat for even-odd): no p, no phase C
+    int bi_fused = 0;   // BiCGSTAB: the fused iteration (four launches, one trailing finish per chunk)
     int fused = 0; // phase A completes the previous iteration's finish (launch_iterations): two launches
                    // per iteration and one trailing finish per chunk
     int pcus = 0;  // persistent kernel: one 1024-thread block on each of min(pcus, CUs) compute units
@@ -40,6 +41,8 @@ constexpr size_t BAR_BYTES = 768;
 struct WsLayout {
     size_t prob, scal, scal2, bar, summary, part, eta64, x64, xlo, r, p, q;
     size_t bscal, rh, sv, tv;   // BiCGSTAB only (0 otherwise)
+    size_t bi_part2, bi_rec;    // ... and its fused iteration's, after everything else
+    size_t least;               // bytes without the fused iteration's pieces (BiCGSTAB; else total)
     size_t eta_o, tmp, w64;     // even-odd only (0 otherwise)
     size_t total;
 };
