@@ -114,11 +114,13 @@ struct Slot {
     std::chrono::steady_clock::time_point t_submit;
 };
 
-// Fixed server-wide launch shapes: results must not depend on the mix.
-static void server_shapes(int inner, int &blk, int &nr_ab) {
-    blk = 256;
-    nr_ab = inner == WD_F64 ? 1 : 2;
-}
+// Fixed server-wide launch shape of the site blocks: results must not depend on
+// the mix.  One rhs per thread, phases A and B with two hops in flight: two rhs
+// and one hop at a time took 19 us per phase for 4^4 x 2 + 8^4 x 1 (4.6 ms the
+// pair of requests, now 3.3 ms; six requests of 4^4 to 14^4 18.1 -> 15.8 ms,
+// even-odd 11.9 -> 10.4 ms), bound by the latency of a chain of hops over few
+// wavefronts.
+constexpr int SERVER_BLOCK = 256;
 
 // Phases A and B of an FP32 or FP64 request without even-odd preconditioning
 // whose xy-planes hold 128..256 sites run on plane blocks (one plane per
@@ -133,13 +135,11 @@ static bool prob_xy(const Prob &pr) { return (pr.sorder[KA] >> 17) & 1; }
 
 // tiles of every kernel kind for one request (vectors of vf sites)
 static void prob_tiles(Prob &pr, int inner, int64_t vf, int nrhs, bool xy) {
-    int blk, nr;
-    server_shapes(inner, blk, nr);
+    constexpr int blk = SERVER_BLOCK;
     for (int k = 0; k < NKIND; ++k) {
         const bool plane = xy && (k == KA || k == KB);
-        const int knr = plane ? 1 : (k == KA || k == KB || k == KEA1 || k == KEB1) ? nr : 1;
         pr.nsb[k] = plane ? (int)(vf / pr.g.S[2]) : (int)((vf + blk - 1) / blk);
-        pr.ng[k] = (k == KC || k == KR1 || k == KN) ? nrhs : (nrhs + knr - 1) / knr;
+        pr.ng[k] = nrhs;
         pr.nt[k] = pr.nsb[k] * pr.ng[k];
         pr.t0[k] = 0;
         pr.sorder[k] = plane ? 1 << 17 : 0;   // plane-blocked tiles, lexicographic planes
@@ -148,8 +148,7 @@ static void prob_tiles(Prob &pr, int inner, int64_t vf, int nrhs, bool xy) {
 
 // launch shapes of the server's kernels, with the grid of every kind
 static LaunchSet server_launch(int inner, int eo, int xy, const int grid[NKIND]) {
-    int blk, nr;
-    server_shapes(inner, blk, nr);
+    constexpr int blk = SERVER_BLOCK;
     LaunchSet ls;
     ls.eo = eo;
     ls.qrec = 1;   // k_phaseA and the even-odd phase A carry the direction as q
@@ -158,12 +157,12 @@ static LaunchSet server_launch(int inner, int eo, int xy, const int grid[NKIND])
     for (int k = 0; k < NKIND; ++k) {
         const bool stencil = k == KA || k == KB || k == KR2 || k == KEA1 || k == KEB1 || k == KER2A;
         ls.k[k].block = blk;
-        ls.k[k].nr = (k == KA || k == KB || k == KEA1 || k == KEB1) ? nr : 1;
+        ls.k[k].nr = 1;
         ls.k[k].remap = stencil ? 1 : 0;
         ls.k[k].grid = grid[k];
+        if (k == KA || k == KB) ls.k[k].ordered = 3;
         if (xy && (k == KA || k == KB)) {
             ls.k[k].xy = 1;
-            ls.k[k].nr = 1;
             ls.k[k].ordered = 5;
             ls.k[k].order = 1 << 17;
         }
