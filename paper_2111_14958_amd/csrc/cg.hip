@@ -75,6 +75,16 @@ __global__ __launch_bounds__(MP ? 512 : 256, (phase_waves<P, NR>())) void k_phas
     phaseB_tile<P, NR, ORD, XY, R12, NT, true, MP>(pr, t_, par, last);
 }
 
+// direction-split phases A and B (phaseA_split_tile), four threads per site
+template <int P, bool R12, bool B>
+__global__ __launch_bounds__(P == P64 ? 512 : 1024) void k_phase_split(const Prob *__restrict__ probs, int nprob, int remap, int par,
+                                                      int edge) {
+    extern __shared__ uint4 split_lds_raw[];
+    WD_KERNEL_PROLOGUE(B ? KB : KA)
+    if constexpr (B) phaseB_split_tile<P, R12>(pr, t_, par, edge, split_lds_raw);
+    else phaseA_split_tile<P, R12>(pr, t_, par, edge, split_lds_raw);
+}
+
 // z-marching phases A and B (zm_tile); dynamic LDS of two plane buffers
 template <int P, int ORD>
 __global__ __launch_bounds__(256) void k_phaseA_zm(const Prob *__restrict__ probs, int nprob, int remap) {
@@ -450,8 +460,23 @@ static void launch_AB_o5(int r12, int nt, int mp, int grid, int blk, hipStream_t
     }
 }
 
+template <int P, bool B>
+static void launch_split(const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int edge) {
+    const dim3 gr(k.grid), bl(k.block);
+    if constexpr (P == P32)
+        if (k.r12) {
+            WD_TIMED_LAUNCH_LDS((k_phase_split<P, true, B>), gr, bl, k.lds, st, d, n, k.remap, par, edge);
+            return;
+        }
+    WD_TIMED_LAUNCH_LDS((k_phase_split<P, false, B>), gr, bl, k.lds, st, d, n, k.remap, par, edge);
+}
+
 template <int P>
 static void launch_A(const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int first) {
+    if (k.split) {
+        launch_split<P, false>(k, st, d, n, par, first);
+        return;
+    }
     if (k.ordered == 5) launch_AB_o5<P, false>(k.r12, k.nt, k.planes > 1, k.grid, k.block, st, d, n, k.remap, par, first);
     else if (k.ordered == 3)
         launch_AB_o<P, 3, false>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, first);
@@ -459,6 +484,10 @@ static void launch_A(const KindShape &k, hipStream_t st, const Prob *d, int n, i
 }
 template <int P>
 static void launch_B(const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int last) {
+    if (k.split) {
+        launch_split<P, true>(k, st, d, n, par, last);
+        return;
+    }
     if (k.ordered == 5) launch_AB_o5<P, true>(k.r12, k.nt, k.planes > 1, k.grid, k.block, st, d, n, k.remap, par, last);
     else if (k.ordered == 3)
         launch_AB_o<P, 3, true>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, last);
@@ -834,6 +863,19 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
                     ks.block = (kp * np + 63) & ~63;
                     ks.order |= kp << 18;
                 }
+                // direction split: at most one plane block per compute unit, or two
+                // of 64 sites.  Whole solves, plain against split: 8^4 FP32 1 / 8
+                // fields 2.10 -> 1.83, 2.55 -> 2.31 ms (16 fields, 1024 blocks, 2.82
+                // -> 2.69; FP16N none), FP64 x 4 2.56 -> 2.35, 10x10x8x8 x 3 2.37 ->
+                // 2.12, 14^4 x 1 (196 blocks) 2.83 -> 2.75 ms; but 12^4 x 2 (288
+                // blocks of 768 threads) 2.97 -> 4.22 ms: the second round of blocks
+                const int npr = (np + 63) & ~63, lds = split_lds_bytes(inner, np), blocks = V / np * nrhs;
+                if (kp == 1 && blocks <= (np == 64 ? 512 : 256) && lds <= 65536 &&
+                    4 * npr <= (inner == WD_F64 ? 512 : 1024)) {
+                    ks.split = 1;
+                    ks.block = 4 * npr;
+                    ks.lds = lds;
+                }
             }
         } else {
             ks.block = 256;
@@ -888,6 +930,7 @@ void plan_persistent(LaunchSet &ls, Prob &pr, int64_t V, int nrhs, int inner, in
         ks.order = ks.xy == 2 ? 0 : ks.order & ~(1 << 17) & ~(7 << 18);
         ks.xy = 0;
         ks.planes = 1;
+        ks.split = 0;
         ks.lds = 0;
         ks.r12 = cus && inner == WD_F32 && pr.U12 != nullptr;
         ks.nt = 0;
@@ -960,7 +1003,7 @@ struct GraphKey {
     KindShape shp[NKIND];
     bool operator<(const GraphKey &o) const { return memcmp(this, &o, sizeof(*this)) < 0; }
 };
-static_assert(sizeof(KindShape) == 11 * sizeof(int), "KindShape must be plain ints (compared bytewise)");
+static_assert(sizeof(KindShape) == 12 * sizeof(int), "KindShape must be plain ints (compared bytewise)");
 
 struct GraphEntry {
     hipGraph_t graph = nullptr;
@@ -1158,9 +1201,10 @@ int cg_run(const wd_gauge *g, double m0, const void *src, void *sol, int nrhs, c
     const int persistent = (p.persistent == 1 && !bicg) ? 1 : 0;
     if (persistent) plan_persistent(ls, hp, V, nrhs, p.inner, p.max_cus);
     for (int k = 0; k < NKIND; ++k)   // kernels launched one by one are compiled for <= 256 threads
-                                      // (multi-plane phases A and B: <= 512)
+                                      // (phases A and B: multi-plane <= 512, direction-split <= 1024)
         WD_CHECK(ls.k[k].block <= 256 || (persistent && (k == KA || k == KB)) ||
-                     (ls.k[k].planes > 1 && ls.k[k].block <= 512 && (k == KA || k == KB)),
+                     (ls.k[k].planes > 1 && ls.k[k].block <= 512 && (k == KA || k == KB)) ||
+                     (ls.k[k].split && ls.k[k].block <= 1024 && (k == KA || k == KB)),
                  WD_EINVAL, "kernel kind %d planned with %d threads per block", k, ls.k[k].block);
     for (int k = 0; k < NKIND; ++k)   // every kind's partial sums fit the buffer
         WD_CHECK(hp.nsb[k] <= (V + 63) / 64, WD_EINVAL, "kernel kind %d has %d site blocks, the partial-sum "

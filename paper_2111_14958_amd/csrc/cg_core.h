@@ -821,6 +821,151 @@ __device__ __forceinline__ void phaseAB_finish(const Prob &pr, const Scal *sin, 
 }
 __device__ __forceinline__ void phaseAB_finish(const Prob &pr) { phaseAB_finish(pr, pr.sc, pr.sc, 0, 0); }
 
+// ------------------------------------------ direction-split phases A and B
+// For launches too small to fill the chip (at most one plane block per compute
+// unit): four groups of threads per plane, one per direction (split_hops), so a
+// block's four memory hops are one round of loads instead of two, the arithmetic
+// of a site runs on four wavefronts instead of one, and the z and t groups work
+// while the plane is staged; group 0 sums (split_sum) and does the phase's
+// epilogue.  Records, partials and the fused finish are those of phaseA_tile and
+// phaseB_tile (plane blocks, one rhs per thread); the hops are added in another
+// order.  LDS: the staged plane, then split_sum's.  A single 8^4 field, FP32: a
+// phase 8.1 -> 7.0 us (launch, records and partials about half of that), a solve
+// 2.10 -> 1.83 ms.
+template <int P> __device__ __forceinline__ typename real_of<P>::type *split_lds(uint4 *lds, int np) {
+    return (typename real_of<P>::type *)((typename LdsSpinor<P>::word *)lds + LdsWords<P>::value * np);
+}
+// the block's tile: site block, rhs, direction group, the thread's place in it and its site (g.V: none)
+__device__ __forceinline__ void split_tile(const Prob &pr, int K, int t, int &sb, int &rhs, int &d, int &i, int &s) {
+    const int npr = (int)blockDim.x >> 2, np = pr.g.S[2];
+    sb = t / pr.ng[K];
+    rhs = t - sb * pr.ng[K];
+    d = __builtin_amdgcn_readfirstlane((int)threadIdx.x / npr);
+    i = (int)threadIdx.x - d * npr;
+    s = i < np ? order_site(pr.g, pr.sorder[K] & 0xffff, sb * np + i) : pr.g.V;
+}
+
+template <int P, bool R12>
+__device__ __forceinline__ void phaseA_split_tile(const Prob &pr, int t, int par, int first, uint4 *lds) {
+    typedef typename real_of<P>::type R;
+    typedef typename LdsSpinor<P>::word W;
+    __shared__ FinShared<1> fs;
+    int sb, rhs, d, i, s;
+    split_tile(pr, KA, t, sb, rhs, d, i, s);
+    FusedFinish<1> ff(pr, fs, rhs, true, par, first);
+    const Geom g = pr.g;
+    const int np = g.S[2];
+    W *xy = (W *)lds;
+    R *sum = split_lds<P>(lds, np);
+    const FieldPtr fr{pr.r, g.V, pr.nrhs}, fq{ff.newq(), g.V, pr.nrhs};
+    const void *U = R12 ? pr.U12 : pr.U_lo;
+    ff.begin();
+    cx<R> acc[12];
+    if (ff.act0) {
+        if (d == 0 && s < g.V) {
+            cx<R> v[12];
+            Spinor<P>::load(fr, rhs, s, v);
+            LdsSpinor<P>::put(xy, np, 0, i, v);
+        }
+        if (s < g.V) split_hops<P, true, R12>(g, d, true, s, U, fr, rhs, xy, s - i, np, acc);
+        ff.reduce();
+        __syncthreads();
+    }
+    const unsigned act = ff.decide();
+    double part[1] = {0.0};
+    if (act) {
+        if (s < g.V) split_hops<P, true, R12>(g, d, false, s, U, fr, rhs, xy, s - i, np, acc);
+        split_sum<R>(d, i, np, i < np, sum, acc);
+        if (d == 0 && s < g.V) {
+            cx<R> self[12], o[12];
+            LdsSpinor<P>::get(xy, np, 0, i, self);
+            wilson_finish<R>((R)pr.diag, self, acc, o);
+            if (!ff.restart(0)) {
+                const R b = (R)ff.beta(0);
+                const FieldPtr fo{ff.oldq(0), g.V, pr.nrhs};
+                cx<R> qo[12];
+                Spinor<P>::load(fo, rhs, s, qo);
+#pragma unroll
+                for (int k = 0; k < 12; ++k) o[k] = {o[k].re + b * qo[k].re, o[k].im + b * qo[k].im};
+            }
+            Spinor<P>::store(fq, rhs, s, o);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) part[0] += (double)norm2(o[k]);
+        }
+        block_sum<1>(part);
+        if (threadIdx.x == 0) part_at(pr, sb, rhs, ff.slot()) = part[0];
+    }
+    ff.store(sb);
+}
+
+template <int P, bool R12>
+__device__ __forceinline__ void phaseB_split_tile(const Prob &pr, int t, int par, int last, uint4 *lds) {
+    typedef typename real_of<P>::type R;
+    constexpr int XP = XPrec<P>::value;
+    typedef typename real_of<XP>::type RX;
+    typedef typename LdsSpinor<P>::word W;
+    __shared__ double sig[1];
+    int sb, rhs, d, i, s;
+    split_tile(pr, KB, t, sb, rhs, d, i, s);
+    const Scal &sc = par == 0 ? pr.sc2[rhs] : pr.sc[rhs];
+    const int aslot = par > 0 ? 2 : 0;
+    if (sc.state != ST_ACTIVE) return;   // uniform over the block
+    const Geom g = pr.g;
+    const int np = g.S[2];
+    W *xy = (W *)lds;
+    R *sum = split_lds<P>(lds, np);
+    const FieldPtr fq{par > 0 ? pr.p : pr.q, g.V, pr.nrhs}, fr{pr.r, g.V, pr.nrhs}, fx{pr.x_lo, g.V, pr.nrhs};
+    const void *U = R12 ? pr.U12 : pr.U_lo;
+    double ps[1][4];
+    fa_issue<1>(pr, rhs, 1u, ps, aslot);
+    cx<R> acc[12], r[12];
+    if (d == 0 && s < g.V) {
+        cx<R> v[12];
+        Spinor<P>::load(fq, rhs, s, v);
+        LdsSpinor<P>::put(xy, np, 0, i, v);
+    }
+    if (s < g.V) split_hops<P, false, R12>(g, d, true, s, U, fq, rhs, xy, s - i, np, acc);
+    fa_reduce<1>(pr, rhs, 1u, ps, sig, aslot);
+    __syncthreads();
+    if (!finite_pos(sig[0])) return;   // broken down; uniform over the block
+    if (s < g.V) split_hops<P, false, R12>(g, d, false, s, U, fq, rhs, xy, s - i, np, acc);
+    if (d == 0 && s < g.V) Spinor<P>::load(fr, rhs, s, r);
+    split_sum<R>(d, i, np, i < np, sum, acc);
+    double part[1] = {0.0};
+    if (d == 0 && s < g.V) {
+        const double al = sc.rho / sig[0];
+        const R a = (R)al;
+        cx<R> q[12], o[12];
+        LdsSpinor<P>::get(xy, np, 0, i, q);
+        wilson_finish<R>((R)pr.diag, q, acc, o);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) r[k] = {r[k].re - a * o[k].re, r[k].im - a * o[k].im};
+        Spinor<P>::store(fr, rhs, s, r);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) part[0] += (double)norm2(r[k]);
+    }
+    // x_lo (every second launch, see phaseB_tile) by group 1, beside group 0's r
+    if (d == 1 && s < g.V && (par != 0 || last)) {
+        cx<R> q[12];
+        cx<RX> x[12];
+        Spinor<XP>::load(fx, rhs, s, x);
+        if (par > 0) {
+            const FieldPtr fo{pr.q, g.V, pr.nrhs};
+            const RX ao = (RX)sc.alpha;
+            Spinor<P>::load(fo, rhs, s, q);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) x[k] = {x[k].re + ao * (RX)q[k].re, x[k].im + ao * (RX)q[k].im};
+        }
+        LdsSpinor<P>::get(xy, np, 0, i, q);
+        const RX ax = (RX)(sc.rho / sig[0]);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) x[k] = {x[k].re + ax * (RX)q[k].re, x[k].im + ax * (RX)q[k].im};
+        Spinor<XP>::store(fx, rhs, s, x);
+    }
+    block_sum<1>(part);
+    if (threadIdx.x == 0) part_at(pr, sb, rhs, 1) = part[0];
+}
+
 // ---------------------------------------------- z-marching phases A and B
 // A tile is a column of xy-planes: one t, one rhs, the planes z0 <= z < z1 of
 // z-chunk c (the chunk count is pr.sorder[K]).  The block walks the column

@@ -19,6 +19,7 @@ struct KindShape {
     int r12 = 0;       // phases A and B: links from the reconstruct-12 copy
     int nt = 0;        // phases A, B and C: nontemporal streaming accesses (FP64)
     int planes = 1;    // phases A and B, plane-blocked: z-adjacent xy-planes per block
+    int split = 0;     // phases A and B, plane-blocked: four groups of threads per plane, one per direction
 };
 struct LaunchSet {
     KindShape k[NKIND];
@@ -46,6 +47,10 @@ struct WsLayout {
     size_t eta_o, tmp, w64;     // even-odd only (0 otherwise)
     size_t total;
 };
+
+// LDS bytes of a direction-split block: the staged plane of np sites and the
+// sums' two buffers (24 reals per site each)
+inline int split_lds_bytes(int prec, int np) { return 3 * np * (prec == WD_F64 ? 192 : 96); }
 
 WsLayout ws_layout(int64_t V, int nrhs, int inner, int method, int eo = 0);
 void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr);

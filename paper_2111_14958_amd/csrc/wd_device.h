@@ -641,6 +641,81 @@ __device__ __forceinline__ void hopping(const Geom &g, int s, const void *U, con
     }
 }
 
+// The two hops of direction MU at site s of one field: acc = (1 + SF gamma) U psi(s
+// + mu) + (1 + SB gamma) U^dag psi(s - mu).  x and y neighbours from the block's
+// LDS plane, z and t neighbours from memory; the loads of both hops are issued
+// together.
+template <int P, bool DAG, int MU, bool R12>
+__device__ __forceinline__ void dir_hops(const Geom &g, int s, const int c[4], const void *U, const FieldPtr &in,
+                                         int rhs, const typename LdsSpinor<P>::word *xy, int plane0, int np,
+                                         cx<typename real_of<P>::type> acc[12]) {
+    typedef typename real_of<P>::type R;
+    constexpr int SF = DAG ? +1 : -1;
+    const int nf = c[MU] == g.L[MU] - 1 ? s - (g.L[MU] - 1) * g.S[MU] : s + g.S[MU];
+    const int nb = c[MU] == 0 ? s + (g.L[MU] - 1) * g.S[MU] : s - g.S[MU];
+    cx<R> uf[9], ub[9], pf[12], pb[12], h[6], w[6];
+    if constexpr (MU < 2) {
+        LdsSpinor<P>::get(xy, np, 0, nf - plane0, pf);
+        LdsSpinor<P>::get(xy, np, 0, nb - plane0, pb);
+    } else {
+        Spinor<P>::load(in, rhs, nf, pf);
+        Spinor<P>::load(in, rhs, nb, pb);
+    }
+    Link<P>::template load<R12>(U, g, MU, s, MU == 3 && c[3] == g.L[3] - 1, uf);
+    Link<P>::template load<R12>(U, g, MU, nb, MU == 3 && c[3] == 0, ub);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) acc[k] = {R(0), R(0)};
+    project<MU, SF>(pf, h);
+    link_mul(uf, h, w);
+    accumulate<MU, SF>(w, acc);
+    project<MU, -SF>(pb, h);
+    link_adj_mul(ub, h, w);
+    accumulate<MU, -SF>(w, acc);
+}
+
+// Direction split: the block has four groups of npr = blockDim.x / 4 threads
+// (whole wavefronts); thread i of group d forms the two hops of direction d at
+// the block's site i, before = the z and t groups, whose neighbours come from
+// memory (they need not wait for the staged plane), else the x and y groups.
+template <int P, bool DAG, bool R12>
+__device__ __forceinline__ void split_hops(const Geom &g, int d, bool before, int s, const void *U, const FieldPtr &in,
+                                           int rhs, const typename LdsSpinor<P>::word *xy, int plane0, int np,
+                                           cx<typename real_of<P>::type> acc[12]) {
+    int c[4];
+    site_coords(g, s, c);
+    if (before) {
+        if (d == 2) dir_hops<P, DAG, 2, R12>(g, s, c, U, in, rhs, xy, plane0, np, acc);
+        else if (d == 3) dir_hops<P, DAG, 3, R12>(g, s, c, U, in, rhs, xy, plane0, np, acc);
+    } else {
+        if (d == 0) dir_hops<P, DAG, 0, R12>(g, s, c, U, in, rhs, xy, plane0, np, acc);
+        else if (d == 1) dir_hops<P, DAG, 1, R12>(g, s, c, U, in, rhs, xy, plane0, np, acc);
+    }
+}
+// The sum of the four groups' acc, valid in group 0: (x + z) + (y + t).  sum:
+// LDS of 2 x 24 x np reals; on: i < np.  Every thread of the block calls it.
+template <typename R>
+__device__ __forceinline__ void split_sum(int d, int i, int np, bool on, R *sum, cx<R> acc[12]) {
+    R *m = sum + (size_t)(d & 1) * 24 * np + i;
+    auto put = [&]() {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            m[(2 * k) * np] = acc[k].re;
+            m[(2 * k + 1) * np] = acc[k].im;
+        }
+    };
+    auto add = [&]() {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) acc[k] = {acc[k].re + m[(2 * k) * np], acc[k].im + m[(2 * k + 1) * np]};
+    };
+    if (d >= 2 && on) put();
+    __syncthreads();
+    if (d < 2 && on) add();
+    if (d == 1 && on) put();   // over the values this thread has just read
+    __syncthreads();
+    m = sum + (size_t)24 * np + i;
+    if (d == 0 && on) add();
+}
+
 // Hopping sum of Eq. (1) at site s for a block that walks a column of
 // xy-planes along z (one rhs, one t).  The block's LDS holds plane z (`xy`,
 // first site plane0, np sites: the x and y neighbours); the thread holds its
