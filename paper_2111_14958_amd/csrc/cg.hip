@@ -42,8 +42,8 @@ namespace wd {
     const Prob &pr = probs[find_prob(probs, nprob, K, b_)];                    \
     const int t_ = b_ - pr.t0[K];
 
-// R12: links from the reconstruct-12 copy (FP32 storage).  NT: nontemporal
-// streaming accesses (FP64 solves larger than the MALL).  k_phaseB completes
+// R12: links from the reconstruct-12 copy (FP32 storage).  POL: cache policy of
+// the streaming accesses (stream_policy).  k_phaseB completes
 // phase A's reduction in its blocks (phaseB_tile with FA), so phase A has no
 // finish launch of its own.  k_phaseA forms the direction as q = D^dagger r +
 // beta q (phaseA_tile with QR): solves that launch it (LaunchSet::qrec) have
@@ -56,23 +56,31 @@ namespace wd {
 // Waves per SIMD asked of the register allocator: 3 for the FP64 kernels with
 // one rhs per thread (<= 168 VGPRs; left to the compiler some take more, which
 // allows 2).
-template <int P, int NR>
-constexpr int phase_waves() {
-    return P == P64 && NR == 1 ? 3 : 1;
+// FP64 site blocks with two hops in flight (order 3): held to two waves, so that
+// the second hop has its registers (phase B loads x_lo and the old q beside r
+// there).  Left to itself the compiler gives up the second hop for waves, which
+// these launches, short of blocks, do not have: whole solves 8 x 4 x 16 x 16 x 6
+// 4.80 -> 4.39 ms, 16 x 3 x 32 x 24 x 4 11.4 -> 10.9 ms, 4^4 2.13 -> 2.00 ms.
+template <int P, int NR, int ORD, bool XY>
+constexpr int phase_waves(bool most) {
+    if (P == P64 && NR == 1 && ORD == 3 && !XY) return 2;
+    return most ? 8 : P == P64 && NR == 1 ? 3 : 1;
 }
+#define WD_PHASE_WAVES \
+    __attribute__((amdgpu_waves_per_eu(phase_waves<P, NR, ORD, XY>(false), phase_waves<P, NR, ORD, XY>(true))))
 
-template <int P, int NR, int ORD, bool XY, bool R12 = false, bool NT = false, bool MP = false>
-__global__ __launch_bounds__(MP ? 512 : 256, (phase_waves<P, NR>())) void k_phaseA(
+template <int P, int NR, int ORD, bool XY, bool R12 = false, int POL = 0, bool MP = false>
+__global__ __launch_bounds__(MP ? 512 : 256) WD_PHASE_WAVES void k_phaseA(
     const Prob *__restrict__ probs, int nprob, int remap, int par, int first) {
     WD_KERNEL_PROLOGUE(KA)
-    phaseA_tile<P, NR, ORD, XY, R12, NT, true, MP>(pr, t_, par, first);
+    phaseA_tile<P, NR, ORD, XY, R12, POL, true, MP>(pr, t_, par, first);
 }
 
-template <int P, int NR, int ORD, bool XY, bool R12 = false, bool NT = false, bool MP = false>
-__global__ __launch_bounds__(MP ? 512 : 256, (phase_waves<P, NR>())) void k_phaseB(
+template <int P, int NR, int ORD, bool XY, bool R12 = false, int POL = 0, bool MP = false>
+__global__ __launch_bounds__(MP ? 512 : 256) WD_PHASE_WAVES void k_phaseB(
     const Prob *__restrict__ probs, int nprob, int remap, int par, int last) {
     WD_KERNEL_PROLOGUE(KB)
-    phaseB_tile<P, NR, ORD, XY, R12, NT, true, MP>(pr, t_, par, last);
+    phaseB_tile<P, NR, ORD, XY, R12, POL, true, MP>(pr, t_, par, last);
 }
 
 // direction-split phases A and B (phaseA_split_tile), four threads per site
@@ -100,10 +108,10 @@ __global__ __launch_bounds__(256) void k_phaseB_zm(const Prob *__restrict__ prob
     zm_tile<P, ORD, true>(pr, t_, (typename LdsSpinor<P>::word *)zm_lds);
 }
 
-template <int P, bool NT = false>
+template <int P>
 __global__ __launch_bounds__(256) void k_phaseC(const Prob *__restrict__ probs, int nprob, int remap) {
     WD_KERNEL_PROLOGUE(KC)
-    phaseC_tile<P, NT>(pr, t_);
+    phaseC_tile<P>(pr, t_);
 }
 
 template <int P>
@@ -374,14 +382,14 @@ static void launch_AB_nt(int nr, int xy, int grid, int blk, hipStream_t st, cons
     const dim3 gr(grid), bl(blk);
     if constexpr (P == P64) {
         if (xy) {
-            if (B) WD_TIMED_LAUNCH((k_phaseB<P, 1, ORD, true, false, true>), gr, bl, st, d, n, remap, par, first);
-            else WD_TIMED_LAUNCH((k_phaseA<P, 1, ORD, true, false, true>), gr, bl, st, d, n, remap, par, first);
+            if (B) WD_TIMED_LAUNCH((k_phaseB<P, 1, ORD, true, false, 1>), gr, bl, st, d, n, remap, par, first);
+            else WD_TIMED_LAUNCH((k_phaseA<P, 1, ORD, true, false, 1>), gr, bl, st, d, n, remap, par, first);
         } else if (nr == 2) {
-            if (B) WD_TIMED_LAUNCH((k_phaseB<P, 2, ORD, false, false, true>), gr, bl, st, d, n, remap, par, first);
-            else WD_TIMED_LAUNCH((k_phaseA<P, 2, ORD, false, false, true>), gr, bl, st, d, n, remap, par, first);
+            if (B) WD_TIMED_LAUNCH((k_phaseB<P, 2, ORD, false, false, 1>), gr, bl, st, d, n, remap, par, first);
+            else WD_TIMED_LAUNCH((k_phaseA<P, 2, ORD, false, false, 1>), gr, bl, st, d, n, remap, par, first);
         } else {
-            if (B) WD_TIMED_LAUNCH((k_phaseB<P, 1, ORD, false, false, true>), gr, bl, st, d, n, remap, par, first);
-            else WD_TIMED_LAUNCH((k_phaseA<P, 1, ORD, false, false, true>), gr, bl, st, d, n, remap, par, first);
+            if (B) WD_TIMED_LAUNCH((k_phaseB<P, 1, ORD, false, false, 1>), gr, bl, st, d, n, remap, par, first);
+            else WD_TIMED_LAUNCH((k_phaseA<P, 1, ORD, false, false, 1>), gr, bl, st, d, n, remap, par, first);
         }
     }
 }
@@ -394,7 +402,7 @@ static void launch_AB_o(int nr, int xy, int lds, int r12, int nt, int grid, int 
         launch_AB_r12<P, ORD, B>(nr, xy, grid, blk, st, d, n, remap, par, first);
         return;
     }
-    if (nt) {
+    if (nt == 1) {
         launch_AB_nt<P, ORD, B>(nr, xy, grid, blk, st, d, n, remap, par, first);
         return;
     }
@@ -427,36 +435,30 @@ static void launch_AB_o(int nr, int xy, int lds, int r12, int nt, int grid, int 
     }
 }
 // hop order 5 (the memory hops z and t first, then the LDS hops x and y):
-// plane-blocked variants with one rhs per thread
+// plane-blocked variants with one rhs per thread, by the streams' cache policy
+template <int P, int POL, bool R12, bool MP, bool B>
+static void launch_AB_5(const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int edge) {
+    const dim3 gr(k.grid), bl(k.block);
+    if (B) WD_TIMED_LAUNCH((k_phaseB<P, 1, 5, true, R12, POL, MP>), gr, bl, st, d, n, k.remap, par, edge);
+    else WD_TIMED_LAUNCH((k_phaseA<P, 1, 5, true, R12, POL, MP>), gr, bl, st, d, n, k.remap, par, edge);
+}
 template <int P, bool B>
-static void launch_AB_o5(int r12, int nt, int mp, int grid, int blk, hipStream_t st, const Prob *d, int n, int remap,
-                         int par, int first) {
-    const dim3 gr(grid), bl(blk);
-    if (mp) {   // several planes per block: FP32 and FP16 storage
-        if constexpr (P != P64) {
-            if (r12) {
-                if constexpr (P == P32) {
-                    if (B) WD_TIMED_LAUNCH((k_phaseB<P, 1, 5, true, true, false, true>), gr, bl, st, d, n, remap, par, first);
-                    else WD_TIMED_LAUNCH((k_phaseA<P, 1, 5, true, true, false, true>), gr, bl, st, d, n, remap, par, first);
-                }
-            } else {
-                if (B) WD_TIMED_LAUNCH((k_phaseB<P, 1, 5, true, false, false, true>), gr, bl, st, d, n, remap, par, first);
-                else WD_TIMED_LAUNCH((k_phaseA<P, 1, 5, true, false, false, true>), gr, bl, st, d, n, remap, par, first);
-            }
-        }
-    } else if (r12) {
-        if constexpr (P == P32) {
-            if (B) WD_TIMED_LAUNCH((k_phaseB<P, 1, 5, true, true>), gr, bl, st, d, n, remap, par, first);
-            else WD_TIMED_LAUNCH((k_phaseA<P, 1, 5, true, true>), gr, bl, st, d, n, remap, par, first);
-        }
-    } else if (nt) {
-        if constexpr (P == P64) {
-            if (B) WD_TIMED_LAUNCH((k_phaseB<P, 1, 5, true, false, true>), gr, bl, st, d, n, remap, par, first);
-            else WD_TIMED_LAUNCH((k_phaseA<P, 1, 5, true, false, true>), gr, bl, st, d, n, remap, par, first);
-        }
+static void launch_AB_o5(const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int edge) {
+    const bool mp = k.planes > 1;   // several planes per block: FP32 and FP16 storage
+    if constexpr (P == P64) {
+        if (k.nt == 0) launch_AB_5<P, 0, false, false, B>(k, st, d, n, par, edge);
+        else if (k.nt == 1) launch_AB_5<P, 1, false, false, B>(k, st, d, n, par, edge);
+        else launch_AB_5<P, 2, false, false, B>(k, st, d, n, par, edge);
+    } else if (P == P32 && k.r12) {
+        if (k.nt == 3) mp ? launch_AB_5<P, 3, P == P32, true, B>(k, st, d, n, par, edge)
+                          : launch_AB_5<P, 3, P == P32, false, B>(k, st, d, n, par, edge);
+        else mp ? launch_AB_5<P, 2, P == P32, true, B>(k, st, d, n, par, edge)
+                : launch_AB_5<P, 2, P == P32, false, B>(k, st, d, n, par, edge);
     } else {
-        if (B) WD_TIMED_LAUNCH((k_phaseB<P, 1, 5, true>), gr, bl, st, d, n, remap, par, first);
-        else WD_TIMED_LAUNCH((k_phaseA<P, 1, 5, true>), gr, bl, st, d, n, remap, par, first);
+        if (k.nt == 3) mp ? launch_AB_5<P, 3, false, true, B>(k, st, d, n, par, edge)
+                          : launch_AB_5<P, 3, false, false, B>(k, st, d, n, par, edge);
+        else mp ? launch_AB_5<P, 2, false, true, B>(k, st, d, n, par, edge)
+                : launch_AB_5<P, 2, false, false, B>(k, st, d, n, par, edge);
     }
 }
 
@@ -477,7 +479,7 @@ static void launch_A(const KindShape &k, hipStream_t st, const Prob *d, int n, i
         launch_split<P, false>(k, st, d, n, par, first);
         return;
     }
-    if (k.ordered == 5) launch_AB_o5<P, false>(k.r12, k.nt, k.planes > 1, k.grid, k.block, st, d, n, k.remap, par, first);
+    if (k.ordered == 5) launch_AB_o5<P, false>(k, st, d, n, par, first);
     else if (k.ordered == 3)
         launch_AB_o<P, 3, false>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, first);
     else launch_AB_o<P, 1, false>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, first);
@@ -488,7 +490,7 @@ static void launch_B(const KindShape &k, hipStream_t st, const Prob *d, int n, i
         launch_split<P, true>(k, st, d, n, par, last);
         return;
     }
-    if (k.ordered == 5) launch_AB_o5<P, true>(k.r12, k.nt, k.planes > 1, k.grid, k.block, st, d, n, k.remap, par, last);
+    if (k.ordered == 5) launch_AB_o5<P, true>(k, st, d, n, par, last);
     else if (k.ordered == 3)
         launch_AB_o<P, 3, true>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, last);
     else launch_AB_o<P, 1, true>(k.nr, k.xy, k.lds, k.r12, k.nt, k.grid, k.block, st, d, n, k.remap, par, last);
@@ -676,8 +678,7 @@ static void launch_kind_tiles(int kind, int inner, const KindShape &k, hipStream
         else launch_B<P16>(k, st, d, nprob, par, first);
         break;
     case KC:
-        if (inner == P64 && k.nt) WD_TIMED_LAUNCH((k_phaseC<P64, true>), dim3(k.grid), dim3(k.block), st, d, nprob, 0);
-        else if (inner == P64) WD_TIMED_LAUNCH(k_phaseC<P64>, dim3(k.grid), dim3(k.block), st, d, nprob, 0);
+        if (inner == P64) WD_TIMED_LAUNCH(k_phaseC<P64>, dim3(k.grid), dim3(k.block), st, d, nprob, 0);
         else if (inner == P32) WD_TIMED_LAUNCH(k_phaseC<P32>, dim3(k.grid), dim3(k.block), st, d, nprob, 0);
         else WD_TIMED_LAUNCH(k_phaseC<P16>, dim3(k.grid), dim3(k.block), st, d, nprob, 0);
         break;
@@ -761,6 +762,28 @@ bool unfused_requested() {
     return v && *v && strcmp(v, "0") != 0;
 }
 
+// bytes of the fields an iteration touches: r, q in two buffers, x_lo
+static size_t iterated_bytes(int inner, int64_t Vf, int nrhs) {
+    return 3 * spinor_bytes(inner, Vf, nrhs) + spinor_bytes(inner == WD_F16N ? WD_F32 : inner, Vf, nrhs);
+}
+
+// Cache policy (see ld) of the phases' streaming accesses, by whether the fields
+// an iteration touches (r, q in two buffers, x_lo) fit the 256 MB MALL.  They do:
+// device-scope accesses (2) leave the L2 to the gathered field: whole solves,
+// plain against them, 12^4 x 12 FP64 12.55 -> 12.28 ms (nontemporal 13.3), 12^4 x
+// 12 FP32 7.21 -> 7.10, 14^4 x 16 FP32 15.7 -> 15.5 ms; FP64 below 128 MB
+// stays plain (0), of which the L2s hold a good part (14^4 x 2 5.62 ms against
+// 5.85, 16^4 x 2 8.06 against 8.20).  They do not: FP64
+// nontemporal (1), 14^4 x 16 plain 33.8, device-scope 34.0, nontemporal 30.8 ms;
+// FP32 and FP16N nontemporal loads with device-scope stores (3), 16^3 x 32 x 6
+// FP32 20.8 -> 19.3 ms (nontemporal both ways 19.9), x 12 FP16N 30.5 -> 29.1 ms.
+// With policy 3 below that size 14^4 x 16 FP32 takes 17.3 ms: it gives up the
+// MALL's copies.
+static int stream_policy(int inner, size_t bytes) {
+    if (bytes <= (size_t)256 << 20) return inner == WD_F64 && bytes < (size_t)128 << 20 ? 0 : 2;
+    return inner == WD_F64 ? 1 : 3;
+}
+
 void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr) {
     const int V = (int)g->V;
     const int np = g->dims[0] * g->dims[1];
@@ -780,8 +803,7 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
                               &sa, &sb, &sr};
     const int Vf = pr.vf;
     ls.eo = pr.eo;
-    // the six vectors of the FP64 iteration exceed the 256 MB MALL
-    const bool mall_exceeded = 6.0 * 192.0 * (double)Vf * nrhs > 256.0 * 1024 * 1024;
+    const int policy = stream_policy(inner, iterated_bytes(inner, Vf, nrhs));
     for (int k = 0; k < NKIND; ++k) {
         KindShape &ks = ls.k[k];
         if (st[k]) {
@@ -819,10 +841,12 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
                 ks.order = nzc;
                 ks.lds = 2 * 6 * np * 16;   // two planes of 6 float4 per site
             }
-            // nontemporal streams: FP64 phases A and B when the solve's fields outgrow the MALL
-            if ((k == KA || k == KB) && inner == WD_F64 && mall_exceeded && ks.xy != 2) {
-                ks.nt = 1;
-                if (ks.nr > 2) ks.nr = 2;
+            // cache policy of phases A and B's streams: the plane-blocked kernels with
+            // hop order 5, and nontemporal streams in the other FP64 ones
+            if ((k == KA || k == KB) && ks.xy != 2 && !pr.eo) {
+                const bool five = ks.xy == 1 && ks.ordered == 5 && ks.nr == 1;
+                ks.nt = five || policy == 1 ? policy : 0;
+                if (ks.nt == 1 && ks.nr > 2) ks.nr = 2;
             }
             // reconstruct-12 links for phases A and B (FP32; plane or site blocks, <= 2 rhs per thread;
             // even-odd: both half-lattice hops of each phase)
@@ -856,7 +880,7 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
             // several z-adjacent planes per block (FP32 / FP16 storage, hop order 5);
             // the block is rounded up to whole wavefronts for the block sums
             ks.planes = 1;
-            if ((k == KA || k == KB) && ks.xy == 1 && ks.nr == 1 && ks.ordered == 5 && !ks.nt && !pr.eo) {
+            if ((k == KA || k == KB) && ks.xy == 1 && ks.nr == 1 && ks.ordered == 5 && !pr.eo) {
                 const int kp = xy_planes(*st[k], geo, inner, 1);
                 if (kp > 1) {
                     ks.planes = kp;
@@ -883,7 +907,6 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
             ks.remap = 0;
             ks.order = 0;
             ks.xy = 0;
-            ks.nt = k == KC && inner == WD_F64 && mall_exceeded && !pr.eo;
         }
         pr.sorder[k] = ks.order;
         pr.nsb[k] = ks.xy == 2 ? ks.order * g->dims[3] : ks.xy ? V / (np * ks.planes) : (Vf + ks.block - 1) / ks.block;

@@ -103,12 +103,10 @@ struct alignas(16) Prob {
     void *w64;                // even-odd: odd-site intermediate of R2 (FP64)
 };
 
-// NT (phase tiles): the streaming accesses (fields each thread reads or writes
-// once) carry the nontemporal hint.  The host sets it for FP64 solves whose
-// fields exceed the 256 MB MALL: there the L2 then keeps more of the
-// neighbouring input planes and phases A, B and C ran 5-9 % faster (14^4, 16
-// rhs), while a single FP64 field, which the MALL holds, ran 6 % slower with
-// it, and FP32/FP16 storage 13-23 % slower.
+// POL (phase tiles): the cache policy (see ld and st) of the streaming accesses,
+// the fields each thread reads or writes once: r and x_lo in phase B, the old
+// and the new q.  The host sets it (stream_policy): 0 for the kernels that are
+// not the default ones.
 
 // precision x_lo is stored in
 template <int P> struct XPrec { static constexpr int value = P; };
@@ -500,7 +498,7 @@ template <int NR> struct FusedFinish {
 // pr.p (par 1), so that phase B can add two iterations' alpha q to x_lo in one
 // pass (see phaseB_tile): the old q is read from the other buffer (in the
 // chunk's first iteration, from the one the field's record names).
-template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, bool NT = false, bool QR = false,
+template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, int POL = 0, bool QR = false,
           bool MP = false>
 __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1, int first = 0) {
     typedef typename real_of<P>::type R;
@@ -557,12 +555,12 @@ __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1,
                         const R b = P == P64 ? beta[j] : (R)ff.beta(j);
                         const FieldPtr fo{ff.oldq(j), g.V, pr.nrhs};
                         cx<R> qo[12];
-                        Spinor<P>::template load<NT>(fo, rhs0 + j, s, qo);
+                        Spinor<P>::template load<POL>(fo, rhs0 + j, s, qo);
 #pragma unroll
                         for (int k = 0; k < 12; ++k) o[k] = {o[k].re + b * qo[k].re, o[k].im + b * qo[k].im};
                     }
                 }
-                Spinor<P>::template store<NT>(fq, rhs0 + j, s, o);
+                Spinor<P>::template store<POL>(fq, rhs0 + j, s, o);
                 double n = 0;
 #pragma unroll
                 for (int k = 0; k < 12; ++k) n += (double)norm2(o[k]);
@@ -645,7 +643,7 @@ __device__ __forceinline__ void fa_reduce(const Prob &pr, int rhs0, unsigned act
 // (the chunk's last iteration): parity 0 adds its own alpha q at once.  A
 // field that freezes after a parity-0 iteration keeps its pending alpha q (xq
 // bit 1) for R1.
-template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, bool NT = false, bool FA = false,
+template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, int POL = 0, bool FA = false,
           bool MP = false>
 __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1, int last = 0) {
     typedef typename real_of<P>::type R;
@@ -699,10 +697,10 @@ __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1,
                 if constexpr (XY) LdsSpinor<P>::get(xy, np, j, threadIdx.x, q);
                 else Spinor<P>::load(fq, rhs0 + j, s, q);
                 wilson_finish<R>((R)pr.diag, q, acc[j], o);
-                Spinor<P>::template load<NT>(fr, rhs0 + j, s, r);
+                Spinor<P>::template load<POL>(fr, rhs0 + j, s, r);
 #pragma unroll
                 for (int k = 0; k < 12; ++k) r[k] = {r[k].re - a * o[k].re, r[k].im - a * o[k].im};
-                Spinor<P>::template store<NT>(fr, rhs0 + j, s, r);
+                Spinor<P>::template store<POL>(fr, rhs0 + j, s, r);
                 double n = 0;
 #pragma unroll
                 for (int k = 0; k < 12; ++k) n += (double)norm2(r[k]);
@@ -710,28 +708,29 @@ __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1,
                 if (!xup) continue;
                 // issued once r is done with (no instruction): three more
                 // spinors loaded ahead of it would cost phase B a wave per SIMD
+                // (FP64 site blocks have waves to spare, see phase_waves)
                 int sx = s;
-                asm volatile("" : "+v"(sx) : "v"(n));
+                if constexpr (XY || P != P64) asm volatile("" : "+v"(sx) : "v"(n));
                 cx<RX> x[12];
-                Spinor<XP>::template load<NT>(fx, rhs0 + j, sx, x);
+                Spinor<XP>::template load<POL>(fx, rhs0 + j, sx, x);
                 if (par > 0) {   // the iteration before's update first
                     const FieldPtr fo{pr.q, g.V, pr.nrhs};
                     const RX ao = (RX)sc[rhs0 + j].alpha;
                     cx<R> qo[12];
-                    Spinor<P>::template load<NT>(fo, rhs0 + j, sx, qo);
+                    Spinor<P>::template load<POL>(fo, rhs0 + j, sx, qo);
 #pragma unroll
                     for (int k = 0; k < 12; ++k) x[k] = {x[k].re + ao * (RX)qo[k].re, x[k].im + ao * (RX)qo[k].im};
                 }
                 // q read again (from LDS, or a line this thread has just read), so
                 // that it is not held meanwhile
                 int tx = XY ? (int)threadIdx.x : sx;
-                asm volatile("" : "+v"(tx) : "v"(x[0].re), "v"(x[11].im));
+                if constexpr (XY || P != P64) asm volatile("" : "+v"(tx) : "v"(x[0].re), "v"(x[11].im));
                 if constexpr (XY) LdsSpinor<P>::get(xy, np, j, tx, q);
                 else Spinor<P>::load(fq, rhs0 + j, tx, q);
                 const RX ax = (RX)al;
 #pragma unroll
                 for (int k = 0; k < 12; ++k) x[k] = {x[k].re + ax * (RX)q[k].re, x[k].im + ax * (RX)q[k].im};
-                Spinor<XP>::template store<NT>(fx, rhs0 + j, s, x);
+                Spinor<XP>::template store<POL>(fx, rhs0 + j, s, x);
             }
         }
     }
@@ -1034,21 +1033,21 @@ __device__ __forceinline__ void zm_tile(const Prob &pr, int t, typename LdsSpino
             if constexpr (B) {   // r -= alpha D q; x_lo += alpha q
                 const R a = (R)pr.sc[rhs].alpha;
                 cx<R> r[12];
-                Spinor<P>::template load<false>(fr, rhs, s, r);
+                Spinor<P>::template load<0>(fr, rhs, s, r);
 #pragma unroll
                 for (int k = 0; k < 12; ++k) r[k] = {r[k].re - a * o[k].re, r[k].im - a * o[k].im};
-                Spinor<P>::template store<false>(fr, rhs, s, r);
+                Spinor<P>::template store<0>(fr, rhs, s, r);
 #pragma unroll
                 for (int k = 0; k < 12; ++k) n += (double)norm2(r[k]);
                 cx<RX> x[12];
-                Spinor<XP>::template load<false>(fx, rhs, s, x);
+                Spinor<XP>::template load<0>(fx, rhs, s, x);
                 const RX ax = (RX)pr.sc[rhs].alpha;
 #pragma unroll
                 for (int k = 0; k < 12; ++k)
                     x[k] = {x[k].re + ax * (RX)self[k].re, x[k].im + ax * (RX)self[k].im};
-                Spinor<XP>::template store<false>(fx, rhs, s, x);
+                Spinor<XP>::template store<0>(fx, rhs, s, x);
             } else {             // q = D^dagger p
-                Spinor<P>::template store<false>(fq, rhs, s, o);
+                Spinor<P>::template store<0>(fq, rhs, s, o);
 #pragma unroll
                 for (int k = 0; k < 12; ++k) n += (double)norm2(o[k]);
             }
@@ -1063,7 +1062,7 @@ __device__ __forceinline__ void zm_tile(const Prob &pr, int t, typename LdsSpino
 
 // ------------------------------------------------------------------ phase C
 // p = r + beta p (or p = r after a restart), streaming, tile = (site block, rhs)
-template <int P, bool NT = false>
+template <int P>
 __device__ __forceinline__ void phaseC_tile(const Prob &pr, int t) {
     typedef typename real_of<P>::type R;
     const int sb = t / pr.nrhs, i = t - sb * pr.nrhs;
@@ -1072,14 +1071,14 @@ __device__ __forceinline__ void phaseC_tile(const Prob &pr, int t) {
     if (c.state != ST_ACTIVE || !c.pending_p || s >= pr.vf) return;
     FieldPtr fr{pr.r, pr.vf, pr.nrhs}, fp{pr.p, pr.vf, pr.nrhs};
     cx<R> r[12], p[12];
-    Spinor<P>::template load<NT>(fr, i, s, r);
+    Spinor<P>::template load<0>(fr, i, s, r);
     if (!c.restart) {
         const R b = (R)c.beta;
-        Spinor<P>::template load<NT>(fp, i, s, p);
+        Spinor<P>::template load<0>(fp, i, s, p);
 #pragma unroll
         for (int k = 0; k < 12; ++k) r[k] = {r[k].re + b * p[k].re, r[k].im + b * p[k].im};
     }
-    Spinor<P>::template store<NT>(fp, i, s, r);
+    Spinor<P>::template store<0>(fp, i, s, r);
 }
 
 // ------------------------------------------------------- reliable update R1

@@ -17,7 +17,7 @@ struct KindShape {
                        // 2 z-marching columns of planes (zm_tile)
     int lds = 0;       // dynamic LDS bytes per block (z-marching)
     int r12 = 0;       // phases A and B: links from the reconstruct-12 copy
-    int nt = 0;        // phases A, B and C: nontemporal streaming accesses (FP64)
+    int nt = 0;        // phases A and B: cache policy of the streaming accesses (stream_policy)
     int planes = 1;    // phases A and B, plane-blocked: z-adjacent xy-planes per block
     int split = 0;     // phases A and B, plane-blocked: four groups of threads per plane, one per direction
 };

@@ -59,16 +59,35 @@ __device__ __forceinline__ gptr<T> at(void *base, size_t plane, uint32_t off) {
     return (gptr<T>)(wave_uniform((gchar *)base + plane) + off);
 }
 
-// Loads and stores of data a kernel touches once.  NT sets the nontemporal
-// hint, which makes the L2 evict these lines first, so that stencil inputs
-// which neighbouring blocks read again stay resident.
-template <bool NT, typename T> __device__ __forceinline__ T ld(gptr<const T> p) {
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
+// Loads and stores of data a kernel touches once, by cache policy:
+//   0  plain
+//   1  nontemporal loads and stores: the L2 evicts the lines first, so that
+//      stencil inputs which neighbouring blocks read again stay resident, and
+//      the MALL does not keep them
+//   2  device-scope loads and stores (sc1): they pass by the L2 and leave it to
+//      the stencil inputs, and the MALL serves and keeps them
+//   3  nontemporal loads, device-scope stores
+// Policies 2 and 3 are buffer instructions on a plane of `bytes` bytes.
+template <int POL> constexpr int ld_aux() { return POL == 2 ? 16 : 2; }
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void *base, size_t plane, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)wave_uniform((gchar *)base + plane), 0, (int)bytes, 0x00027000);
 }
-template <bool NT, typename T> __device__ __forceinline__ void st(gptr<T> p, T v) {
-    if constexpr (NT) __builtin_nontemporal_store(v, p);
-    else *p = v;
+template <int POL, typename T>
+__device__ __forceinline__ T ld(const void *base, size_t plane, uint32_t off, uint32_t bytes) {
+    if constexpr (POL == 0) return *at<T>(base, plane, off);
+    else if constexpr (POL == 1) return __builtin_nontemporal_load(at<T>(base, plane, off));
+    else if constexpr (sizeof(T) == 16)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(plane_rsrc(base, plane, bytes), off, 0, ld_aux<POL>()));
+    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(plane_rsrc(base, plane, bytes), off, 0, ld_aux<POL>()));
+}
+template <int POL, typename T>
+__device__ __forceinline__ void st(void *base, size_t plane, uint32_t off, uint32_t bytes, T v) {
+    if constexpr (POL == 0) *at<T>(base, plane, off) = v;
+    else if constexpr (POL == 1) __builtin_nontemporal_store(v, at<T>(base, plane, off));
+    else if constexpr (sizeof(T) == 16)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, v), plane_rsrc(base, plane, bytes), off, 0, 16);
+    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), plane_rsrc(base, plane, bytes), off, 0, 16);
 }
 
 template <int P> struct real_of { typedef float type; };
@@ -160,44 +179,43 @@ template <int P> struct Spinor;
 template <> struct Spinor<P64> {
     typedef double R;
     static constexpr int BYTES_PER_SITE = 192;
-    template <bool NT = false>
+    template <int POL = 0>
     __device__ static __forceinline__ void load(const FieldPtr &f, int r, int s, cx<R> o[12]) {
         const size_t pb = (size_t)f.V * 16;
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
-            const d2v v = ld<NT>(at<d2v>((const void *)f.p, (size_t)(r * 12 + k) * pb, (uint32_t)s * 16u));
+            const d2v v = ld<POL, d2v>((const void *)f.p, (size_t)(r * 12 + k) * pb, (uint32_t)s * 16u, (uint32_t)f.V * 16u);
             o[k] = {v.x, v.y};
         }
     }
-    template <bool NT = false>
+    template <int POL = 0>
     __device__ static __forceinline__ void store(const FieldPtr &f, int r, int s, const cx<R> o[12]) {
         const size_t pb = (size_t)f.V * 16;
 #pragma unroll
         for (int k = 0; k < 12; ++k)
-            st<NT>(at<d2v>(f.p, (size_t)(r * 12 + k) * pb, (uint32_t)s * 16u), d2v{o[k].re, o[k].im});
+            st<POL, d2v>(f.p, (size_t)(r * 12 + k) * pb, (uint32_t)s * 16u, (uint32_t)f.V * 16u, d2v{o[k].re, o[k].im});
     }
 };
 
 template <> struct Spinor<P32> {
     typedef float R;
     static constexpr int BYTES_PER_SITE = 96;
-    template <bool NT = false>
+    template <int POL = 0>
     __device__ static __forceinline__ void load(const FieldPtr &f, int r, int s, cx<R> o[12]) {
         const size_t pb = (size_t)f.V * 16;
 #pragma unroll
         for (int j = 0; j < 6; ++j) {
-            const f4v v = ld<NT>(at<f4v>((const void *)f.p, (size_t)(r * 6 + j) * pb, (uint32_t)s * 16u));
+            const f4v v = ld<POL, f4v>((const void *)f.p, (size_t)(r * 6 + j) * pb, (uint32_t)s * 16u, (uint32_t)f.V * 16u);
             o[2 * j] = {v.x, v.y};
             o[2 * j + 1] = {v.z, v.w};
         }
     }
-    template <bool NT = false>
+    template <int POL = 0>
     __device__ static __forceinline__ void store(const FieldPtr &f, int r, int s, const cx<R> o[12]) {
         const size_t pb = (size_t)f.V * 16;
 #pragma unroll
         for (int j = 0; j < 6; ++j)
-            st<NT>(at<f4v>(f.p, (size_t)(r * 6 + j) * pb, (uint32_t)s * 16u),
-                   f4v{o[2 * j].re, o[2 * j].im, o[2 * j + 1].re, o[2 * j + 1].im});
+            st<POL, f4v>(f.p, (size_t)(r * 6 + j) * pb, (uint32_t)s * 16u, (uint32_t)f.V * 16u, f4v{o[2 * j].re, o[2 * j].im, o[2 * j + 1].re, o[2 * j + 1].im});
     }
 };
 
@@ -208,13 +226,13 @@ template <> struct Spinor<P16> {
     __device__ static __forceinline__ size_t norm_plane(const FieldPtr &f, int r) {
         return (size_t)f.nrhs * 3 * f.V * 16 + (size_t)r * f.V * 4;
     }
-    template <bool NT = false>
+    template <int POL = 0>
     __device__ static __forceinline__ void load(const FieldPtr &f, int r, int s, cx<R> o[12]) {
         const size_t pb = (size_t)f.V * 16;
-        const float n = ld<NT>(at<float>((const void *)f.p, norm_plane(f, r), (uint32_t)s * 4u));
+        const float n = ld<POL, float>((const void *)f.p, norm_plane(f, r), (uint32_t)s * 4u, (uint32_t)f.V * 4u);
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            const half8v v = ld<NT>(at<half8v>((const void *)f.p, (size_t)(r * 3 + j) * pb, (uint32_t)s * 16u));
+            const half8v v = ld<POL, half8v>((const void *)f.p, (size_t)(r * 3 + j) * pb, (uint32_t)s * 16u, (uint32_t)f.V * 16u);
 #pragma unroll
             for (int k = 0; k < 4; ++k) o[4 * j + k] = {n * (float)v[2 * k], n * (float)v[2 * k + 1]};
         }
@@ -223,7 +241,7 @@ template <> struct Spinor<P16> {
     // division per site); the scaled value q = v inv is the FP32 product, or
     // the FP32 quotient v / norm where 1 / norm overflows (norm < 2^-128);
     // code = half(q), rounded to nearest even.  Returns the stored values in o.
-    template <bool NT = false>
+    template <int POL = 0>
     __device__ static __forceinline__ void store(const FieldPtr &f, int r, int s, cx<R> o[12]) {
         float n = 0.f;
 #pragma unroll
@@ -256,9 +274,9 @@ template <> struct Spinor<P16> {
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) o[4 * j + k] = {n * (float)v[2 * k], n * (float)v[2 * k + 1]};
-            st<NT>(at<half8v>(f.p, (size_t)(r * 3 + j) * pb, (uint32_t)s * 16u), v);
+            st<POL, half8v>(f.p, (size_t)(r * 3 + j) * pb, (uint32_t)s * 16u, (uint32_t)f.V * 16u, v);
         }
-        st<NT>(at<float>(f.p, norm_plane(f, r), (uint32_t)s * 4u), n);
+        st<POL, float>(f.p, norm_plane(f, r), (uint32_t)s * 4u, (uint32_t)f.V * 4u, n);
     }
 };
 
