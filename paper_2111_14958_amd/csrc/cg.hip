@@ -863,10 +863,16 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
             }
             // even-odd: the phases' half-lattice hops on half-plane blocks (the
             // Lx Ly / 2 sites of one parity on an xy-plane, 64..256 of them),
-            // one rhs per thread, hop order 5
+            // one rhs per thread, hop order 5.  FP16N, whose coding keeps the
+            // phases bound by issue: not between one and four blocks per compute
+            // unit.  Whole solves, site against half-plane blocks: 16^3 x 32 x 1
+            // (512 blocks) 4.54 -> 5.28 ms, 16^4 x 2 3.87 -> 4.33 ms; 14^4 x 1
+            // (196) 3.54 -> 3.28, 16^3 x 32 x 4 (2048) 9.25 -> 9.08 ms
             if (pr.eo && (k == KA || k == KB || k == KEA1 || k == KEB1)) {
                 const int nh = np / 2;
-                ks.xy = st[k]->xylds && nh >= 64 && nh <= 256 ? 1 : 0;
+                const int64_t hb = (int64_t)V / np * nrhs;
+                const bool idle = inner == WD_F16N && hb > 256 && hb < 1024;
+                ks.xy = st[k]->xylds && nh >= 64 && nh <= 256 && !idle ? 1 : 0;
                 ks.order = 0;
                 if (ks.xy) {
                     ks.block = (nh + 63) & ~63;

@@ -44,8 +44,8 @@ static bool g_loaded = false;
 // hops that read memory first), 256-thread blocks.
 // The plane-blocked LDS variants are used where an xy-plane has at most 256
 // sites (else the site-blocked kernels).  One rhs per thread everywhere.
-// Operator kernel: plane-blocked, two z-adjacent planes per block in FP32
-// with 8 or more rhs.
+// Operator kernel: plane-blocked, two z-adjacent planes per block in FP32 and
+// FP16 storage with 8 or more rhs.
 // CG phase kernels: plane-blocked in FP32 and FP64, one plane per block or two
 // (cg_two_planes); in FP16N by fp16_planes.  The reliable-update kernel:
 // plane-blocked.
@@ -60,17 +60,18 @@ int encode_order(const Shape &s) {
 // FP16N phases A and B on plane blocks rather than site blocks.  The decoding
 // and coding of FP16N make the phases bound by issue as much as by memory, so
 // lanes left idle by a plane that does not fill its wavefronts cost more than
-// the x and y neighbours from LDS save: planes of more than 128 sites, 7/8 of
-// the lanes in use, and three blocks or more per compute unit.  Whole solves,
-// site against plane blocks: 16 x 16 planes (16^3 x 32, 12 fields) 33.4 -> 30.8
-// ms, 13 x 14 (16 x 24 of them, 4 fields) 7.6 -> 6.9 ms; but 14 x 14 (196 of
-// 256 lanes; 14^4, 16 fields) 12.4 -> 12.9 ms, 16 x 12 (192 planes, 3 fields)
-// 3.9 -> 4.3 ms.  One field is bound by latency, where planes win at every
+// the x and y neighbours from LDS save: 7/8 of the lanes in use, and planes of
+// more than 192 sites with blocks for half the compute units, or of more than 128
+// with three blocks or more per compute unit.  Whole solves, site against plane blocks: 16 x 16 planes (16^3 x 32, 12
+// fields) 33.4 -> 30.8, (16^4, 2 fields) 4.42 -> 4.13, (16 x 16 x 8 x 8, 2 fields)
+// 2.89 -> 2.81 ms, 15 x 15 (15 x 15 x 8 x 8, 4 fields) 3.24 -> 3.05 ms, 13 x 14 (16 x
+// 24 of them, 4 fields) 7.9 -> 6.8 ms; but 14 x 14 (196 of 256 lanes; 14^4, 4
+// fields) 5.1 -> 5.2 ms, 16 x 12 (192 planes, 3 fields) 4.15 -> 4.42 ms.  One field is bound by latency, where planes win at every
 // size (8^4 2.6 -> 2.5 ms, 12^4 2.9 -> 2.6 ms, 14^4 3.0 -> 2.9 ms).
 static bool fp16_planes(const int L[4], int nrhs) {
     const int np = L[0] * L[1], lanes = (np + 63) / 64 * 64;
     const int64_t blocks = (int64_t)L[2] * L[3] * nrhs;
-    return nrhs == 1 || (np > 128 && 8 * np >= 7 * lanes && blocks >= 768);
+    return nrhs == 1 || (8 * np >= 7 * lanes && ((np > 192 && blocks >= 128) || (np > 128 && blocks >= 768)));
 }
 
 // Planes per block of phases A and B (FP32, FP16N): two where a plane has 256
@@ -100,16 +101,21 @@ Shape default_shape(const ShapeKey &k) {
         // reconstruct-12 links (45 vs 48.5 us; 50 vs 49 us on complete links)
         s.nr = 1;
         s.xylds = 1;
-        if (prec == WD_F16N) s.strip = 0;
         // memory hops (z, t) first: 47.6 -> 45.0 us FP32, 99 -> 97 us FP64
-        // (fabric reads 242 -> 196 MB); FP16 storage unchanged
+        // (fabric reads 242 -> 196 MB).  FP16 storage with z-strips: planes of 224
+        // sites or more (16 x 16, 32 x 12 of them 75 -> 69 us, x 16 fields 91 ->
+        // 84; 15 x 15 as 16 x 16); smaller ones gain nothing by it (16 x 12, 12
+        // fields 28.5 -> 29.3 us) and keep the lexicographic order
+        if (prec == WD_F16N && k.L[0] * k.L[1] < 224) s.strip = 0;
         else s.ordered = 5;
         // FP32 with 8 or more rhs: two z-adjacent planes per block (a 14 x 14
         // plane fills 196 of 256 lanes, two fill 392 of 448): 14^4 x 16 rhs
         // 45.1-45.9 -> 42.7-44.5 us.  With one field the halved block count
-        // costs more than it saves (14^4: 7.1 -> 7.7 us, 12^4: 6.5 -> 6.9 us);
-        // FP16 storage gains 1 % (kept at one plane)
-        if (prec == WD_F32 && nrhs >= 8) s.planes = 2;
+        // costs more than it saves (14^4: 7.1 -> 7.7 us, 12^4: 6.5 -> 6.9 us).
+        // FP16 storage alike: 12^4 x 12 17.1 -> 15.8, 13 x 14 planes 17.5 -> 16.2,
+        // 14^4 x 16 32.3 -> 31.9, 16^3 x 32 x 12 69 -> 65 us (both rules: 78.5 ->
+        // 76.6 us over rotating buffers), 8 x 8 planes the same
+        if (prec != WD_F64 && nrhs >= 8) s.planes = 2;
     } else if (fam == FAM_CG_R) {
         s.nr = 1;
         s.xylds = 1;
