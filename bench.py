@@ -201,7 +201,7 @@ def main():
         nr = min(sh["rhs_per_thread"], 2) if xy else sh["rhs_per_thread"]
         mp = bool(xy) and nr == 1 and sh["hop_order"] == 5 and sh.get("xy_planes", 1) > 1
         # cache policy of the streams: r, q twice and x_lo against the 256 MB MALL
-        policy = (2 if 4 * 96 * V * nrhs <= 256 << 20 else 3) if xy and nr == 1 and sh["hop_order"] == 5 else 0
+        policy = (0 if 4 * 96 * V * nrhs <= 256 << 20 else 3) if xy and nr == 1 and sh["hop_order"] == 5 else 0
         kernel_symbol = "wd::k_%s<1, %d, %d, %s, true, %d, %s>" % (
             dom_name[3:], nr, sh["hop_order"] if sh["hop_order"] in (3, 5) else 1, "true" if xy else "false",
             policy,

@@ -452,13 +452,13 @@ static void launch_AB_o5(const KindShape &k, hipStream_t st, const Prob *d, int 
     } else if (P == P32 && k.r12) {
         if (k.nt == 3) mp ? launch_AB_5<P, 3, P == P32, true, B>(k, st, d, n, par, edge)
                           : launch_AB_5<P, 3, P == P32, false, B>(k, st, d, n, par, edge);
-        else mp ? launch_AB_5<P, 2, P == P32, true, B>(k, st, d, n, par, edge)
-                : launch_AB_5<P, 2, P == P32, false, B>(k, st, d, n, par, edge);
+        else mp ? launch_AB_5<P, 0, P == P32, true, B>(k, st, d, n, par, edge)
+                : launch_AB_5<P, 0, P == P32, false, B>(k, st, d, n, par, edge);
     } else {
         if (k.nt == 3) mp ? launch_AB_5<P, 3, false, true, B>(k, st, d, n, par, edge)
                           : launch_AB_5<P, 3, false, false, B>(k, st, d, n, par, edge);
-        else mp ? launch_AB_5<P, 2, false, true, B>(k, st, d, n, par, edge)
-                : launch_AB_5<P, 2, false, false, B>(k, st, d, n, par, edge);
+        else mp ? launch_AB_5<P, 0, false, true, B>(k, st, d, n, par, edge)
+                : launch_AB_5<P, 0, false, false, B>(k, st, d, n, par, edge);
     }
 }
 
@@ -769,18 +769,18 @@ static size_t iterated_bytes(int inner, int64_t Vf, int nrhs) {
 
 // Cache policy (see ld) of the phases' streaming accesses, by whether the fields
 // an iteration touches (r, q in two buffers, x_lo) fit the 256 MB MALL.  They do:
-// device-scope accesses (2) leave the L2 to the gathered field: whole solves,
-// plain against them, 12^4 x 12 FP64 12.55 -> 12.28 ms (nontemporal 13.3), 12^4 x
-// 12 FP32 7.21 -> 7.10, 14^4 x 16 FP32 15.7 -> 15.5 ms; FP64 below 128 MB
-// stays plain (0), of which the L2s hold a good part (14^4 x 2 5.62 ms against
-// 5.85, 16^4 x 2 8.06 against 8.20).  They do not: FP64
-// nontemporal (1), 14^4 x 16 plain 33.8, device-scope 34.0, nontemporal 30.8 ms;
-// FP32 and FP16N nontemporal loads with device-scope stores (3), 16^3 x 32 x 6
-// FP32 20.8 -> 19.3 ms (nontemporal both ways 19.9), x 12 FP16N 30.5 -> 29.1 ms.
-// With policy 3 below that size 14^4 x 16 FP32 takes 17.3 ms: it gives up the
-// MALL's copies.
+// plain (0), but device-scope accesses (2) in FP64 from 128 MB on, which leave
+// the L2 to the gathered field: whole solves 12^4 x 12 plain 12.55, device-scope
+// 12.28 ms (nontemporal 13.3); 14^4 x 2, of which the L2s hold a good part, 5.62
+// against 5.85 ms.  In FP32 device-scope accesses are not kept: 14^4 x 16 15.7 ->
+// 15.5 ms, but 14 x 10 x 12 x 24 x 5 6.54 -> 7.02, 8 x 8 x 14 x 28 x 10 9.8 -> 10.4
+// ms.  They do not fit: FP64 nontemporal (1), 14^4 x 16 plain 33.8, device-scope
+// 34.0, nontemporal 30.8 ms; FP32 and FP16N nontemporal loads with device-scope
+// stores (3), 16^3 x 32 x 6 FP32 20.8 -> 19.3 ms (nontemporal both ways 19.9), x 12
+// FP16N 30.5 -> 29.1 ms; below that size 14^4 x 16 FP32 takes 17.3 ms with it: it
+// gives up the MALL's copies.
 static int stream_policy(int inner, size_t bytes) {
-    if (bytes <= (size_t)256 << 20) return inner == WD_F64 && bytes < (size_t)128 << 20 ? 0 : 2;
+    if (bytes <= (size_t)256 << 20) return inner == WD_F64 && bytes >= (size_t)128 << 20 ? 2 : 0;
     return inner == WD_F64 ? 1 : 3;
 }
 
