@@ -22,10 +22,14 @@
 //   F5  omega, rho = <r_hat, s> - omega <r_hat, t>, beta;  x += alpha p + omega s,
 //       r = s - omega t,  p = r + beta (p - omega v),  |r|^2
 // rho of the new residual is known before it is formed, so S5 and the next S1
-// are one pass (8 spinor streams instead of 11).  A field whose new rho is a
-// near breakdown has p = r to the order of that rho, and F2 sets r_hat = r,
-// rho = |r|^2.  After a reliable update S1 sets p = r_hat = r once per chunk,
-// and a trailing finish closes a chunk's last iteration into the final records.
+// are one pass (8 spinor streams instead of 11).  The test for a near breakdown
+// needs |r|^2, which F2 completes when p is formed already, so a field that
+// restarts sits out the rest of that round of launches and S3 sets p = r_hat = r
+// (F5's p cannot stay: p - r = rho / (omega <r_hat, v>) (p_old - omega v), and
+// <r_hat, v> is small where the rho before was).  At a chunk's end a trailing
+// finish closes the last iteration into the final records, and the next chunk's
+// S1 sets p = r_hat = r, as it does after a reliable update: the iterates are the
+// same wherever chunks end.
 // The five-stage iteration remains for workspaces without the fused one's
 // records.  12^4 x 4 FP32, where launches and latency bound: a solve 4.36 -> 3.61
 // ms, 3.33 ms with the last chunk cut to the estimated need.
@@ -54,7 +58,7 @@ struct alignas(16) BiRec {
     double wr, wi;   // omega
     double br, bi;   // beta
     double rh2, r2;  // |r_hat|^2, |r|^2
-    int state, iters, since_ru, restart;
+    int state, iters, since_ru, restart;   // restart: the field restarts in this round of launches
 };
 // columns of the fused iteration's partials: pr.part slots 0, 1 <r_hat, v>, 2
 // |r|^2; pr.part2 <t, s>, <t, t>, <r_hat, s>, <r_hat, t>
@@ -80,7 +84,7 @@ __device__ __forceinline__ void bi_end(const Prob &pr, const BiRec &c, double st
     o.ar = c.ar, o.ai = c.ai, o.wr = c.wr, o.wi = c.wi, o.br = c.br, o.bi = c.bi;
     o.rr = c.rr, o.ri = c.ri, o.rh2 = c.rh2, o.r2 = c.r2;
     o.state = c.state, o.iters = c.iters, o.since_ru = c.since_ru, o.restart = 0;
-    if (o.state != ST_ACTIVE) return;
+    if (o.state != ST_ACTIVE || c.restart) return;   // a restart is no iteration
     o.r2 = r2;
     o.iters += 1;
     o.since_ru += 1;
@@ -97,8 +101,8 @@ __device__ __forceinline__ void bi_end(const Prob &pr, const BiRec &c, double st
 
 // The finish of the previous iteration inside F2's blocks: begin issues the
 // loads (before the plane staging, whose latency covers them), reduce (before
-// its barrier) sums |r|^2, decide gives the fields that iterate and, in rst,
-// those that take r as their r_hat.  first: the records are final.
+// its barrier) sums |r|^2, decide gives the fields that iterate (not those that
+// restart).  first: the records are final.
 template <int NR> struct BiBegin {
     const Prob &pr;
     const int rhs0, first;
@@ -117,10 +121,10 @@ template <int NR> struct BiBegin {
     __device__ __forceinline__ void reduce(double *r2) {
         if (!first && act0) col_reduce<NR>(pr, rhs0, act0, a, r2, BI_R2, pr.nsb[KS5]);
     }
-    __device__ __forceinline__ unsigned decide(int sb, const double *r2, int *what, unsigned *rst) {
+    __device__ __forceinline__ unsigned decide(int sb, const double *r2, int *go) {
         if (threadIdx.x < NR) {
             const int j = threadIdx.x, i = rhs0 + j;
-            what[j] = 0;
+            go[j] = 0;
             if (i < pr.nrhs) {
                 BiRec o;
                 if (first) {   // S1 has formed p and r_hat of a field that restarts
@@ -133,21 +137,29 @@ template <int NR> struct BiBegin {
                 } else {
                     bi_end(pr, pr.recm[i], pr.sc[i].stop2, act0 >> j & 1 ? r2[j] : 0.0, o);
                 }
-                what[j] = (o.state == ST_ACTIVE ? 1 : 0) | (o.restart ? 2 : 0);
+                go[j] = o.state == ST_ACTIVE && !o.restart;
                 if (sb == 0) pr.rec2[i] = o;
             }
         }
         __syncthreads();
-        unsigned act = 0, rs = 0;
+        unsigned act = 0;
 #pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            if (what[j] & 1) act |= 1u << j;
-            if (what[j] & 2) rs |= 1u << j;
-        }
-        *rst = rs;
+        for (int j = 0; j < NR; ++j)
+            if (go[j]) act |= 1u << j;
         return act;
     }
 };
+
+// p = r_hat = r at site s of field i
+template <int P>
+__device__ __forceinline__ void bi_restart(const Prob &pr, int i, int s) {
+    typedef typename real_of<P>::type R;
+    FieldPtr fr{pr.r, pr.g.V, pr.nrhs}, fp{pr.p, pr.g.V, pr.nrhs}, fh{pr.rh, pr.g.V, pr.nrhs};
+    cx<R> r[12];
+    Spinor<P>::load(fr, i, s, r);
+    Spinor<P>::store(fh, i, s, r);
+    Spinor<P>::store(fp, i, s, r);
+}
 
 // ------------------------------------------------------------- S1, streaming
 template <int P>
@@ -157,18 +169,13 @@ __device__ __forceinline__ void bi1_tile(const Prob &pr, int t) {
     const int s = sb * blockDim.x + threadIdx.x;
     const Scal &c = pr.sc[i];
     if (c.state != ST_ACTIVE || !c.pending_p || s >= pr.g.V) return;
+    if (c.restart) {
+        bi_restart<P>(pr, i, s);
+        return;
+    }
     FieldPtr fr{pr.r, pr.g.V, pr.nrhs}, fp{pr.p, pr.g.V, pr.nrhs};
     cx<R> r[12];
     Spinor<P>::load(fr, i, s, r);
-    if (c.restart) {
-        FieldPtr fh{pr.rh, pr.g.V, pr.nrhs};
-        cx<R> rr[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) rr[k] = r[k];
-        Spinor<P>::store(fh, i, s, rr);
-        Spinor<P>::store(fp, i, s, r);
-        return;
-    }
     FieldPtr fv{pr.v, pr.g.V, pr.nrhs};
     const dc b = ld(pr.bs[i].beta), w = ld(pr.bs[i].omega);
     const R br = (R)b.re, bi = (R)b.im, wr = (R)w.re, wi = (R)w.im;
@@ -201,14 +208,15 @@ __device__ __forceinline__ void bi_stencil_tile(const Prob &pr, int t, int first
     int sb, grp, s;
     stencil_tile<XY>(pr, K, t, sb, grp, s);
     const int rhs0 = grp * NR;
-    unsigned act = 0, rst = 0;
-    BiBegin<NR> bb(pr, F && !S4 ? rhs0 : 0, first);
+    unsigned act = 0;
+    BiBegin<NR> bb(pr, rhs0, F && !S4 ? first : 1);   // used by F2 alone (first: no fused records to read)
     __shared__ double r2[NR];
-    __shared__ int what[NR];
+    __shared__ int go[NR];
     if constexpr (F && S4) {
 #pragma unroll
         for (int j = 0; j < NR; ++j)
-            if (rhs0 + j < pr.nrhs && pr.rec3[rhs0 + j].state == ST_ACTIVE) act |= 1u << j;
+            if (rhs0 + j < pr.nrhs && pr.rec3[rhs0 + j].state == ST_ACTIVE && !pr.rec3[rhs0 + j].restart)
+                act |= 1u << j;
     } else if constexpr (F) {
         act = bb.act0;
         bb.begin();
@@ -227,7 +235,7 @@ __device__ __forceinline__ void bi_stencil_tile(const Prob &pr, int t, int first
             bb.reduce(r2);
             __syncthreads();
         }
-        act = bb.decide(sb, r2, what, &rst);
+        act = bb.decide(sb, r2, go);
     } else if (XY && act) stage_plane<P, NR>(fin, rhs0, act, s, g.V, xy, np);   // act is uniform over the block
     if (act && s < g.V) {
         FieldPtr fh{pr.rh, g.V, pr.nrhs};
@@ -246,13 +254,6 @@ __device__ __forceinline__ void bi_stencil_tile(const Prob &pr, int t, int first
                 if (S4) {
 #pragma unroll
                     for (int k = 0; k < 12; ++k) a[k] = self[k];   // s
-                } else if (F && (rst >> j & 1)) {                   // r_hat = r
-                    const FieldPtr fr{pr.r, g.V, pr.nrhs};
-                    Spinor<P>::load(fr, rhs0 + j, s, a);
-                    cx<R> h[12];
-#pragma unroll
-                    for (int k = 0; k < 12; ++k) h[k] = a[k];
-                    Spinor<P>::store(fh, rhs0 + j, s, h);
                 } else {
                     Spinor<P>::load(fh, rhs0 + j, s, a);            // r_hat
                 }
@@ -342,7 +343,8 @@ __device__ __forceinline__ void bi4_finish(const Prob &pr) {
 }
 
 // ------------------------------------------------------------- S3, streaming
-// F (the fused iteration): alpha formed here from F2's sums
+// F (the fused iteration): alpha formed here from F2's sums; a field that restarts
+// gets p = r_hat = r instead
 template <int P, bool F = false>
 __device__ __forceinline__ void bi3_tile(const Prob &pr, int t) {
     typedef typename real_of<P>::type R;
@@ -353,7 +355,7 @@ __device__ __forceinline__ void bi3_tile(const Prob &pr, int t) {
         __shared__ double sum[2], al[2];
         __shared__ int go;
         const BiRec &c = pr.rec2[i];
-        const bool live = c.state == ST_ACTIVE;   // uniform over the block
+        const bool live = c.state == ST_ACTIVE && !c.restart;   // uniform over the block
         const int w = threadIdx.x >> 6;
         if (live && w < 2) {
             const double x = wave_col_sum(part_col(pr, i, w), pr.nsb[KS2]);
@@ -368,17 +370,18 @@ __device__ __forceinline__ void bi3_tile(const Prob &pr, int t) {
                 if (!dfinite(rv) || (rv.re == 0.0 && rv.im == 0.0)) state = ST_BREAKDOWN;
                 else na = ddiv(dc{c.rr, c.ri}, rv);
             }
-            go = state == ST_ACTIVE;
+            go = live && state == ST_ACTIVE;
             al[0] = na.re;
             al[1] = na.im;
             if (sb == 0) {
                 BiRec &o = pr.rec3[i];
                 o.rr = c.rr, o.ri = c.ri, o.ar = na.re, o.ai = na.im, o.wr = c.wr, o.wi = c.wi;
                 o.br = c.br, o.bi = c.bi, o.rh2 = c.rh2, o.r2 = c.r2;
-                o.state = state, o.iters = c.iters, o.since_ru = c.since_ru, o.restart = 0;
+                o.state = state, o.iters = c.iters, o.since_ru = c.since_ru, o.restart = c.restart;
             }
         }
         __syncthreads();
+        if (c.restart && s < pr.g.V) bi_restart<P>(pr, i, s);
         if (!go || s >= pr.g.V) return;
         a = dc{al[0], al[1]};
     } else {
@@ -453,7 +456,7 @@ __device__ __forceinline__ void bi5f_tile(const Prob &pr, int t) {
     __shared__ double sum[BI_NP2], sc[6];
     __shared__ int go;
     const BiRec &c = pr.rec3[i];
-    const bool live = c.state == ST_ACTIVE;   // uniform over the block
+    const bool live = c.state == ST_ACTIVE && !c.restart;   // uniform over the block
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     if (live)
         for (int k = w; k < BI_NP2; k += nw) {
@@ -474,13 +477,13 @@ __device__ __forceinline__ void bi5f_tile(const Prob &pr, int t) {
                 be = dmul(ddiv(rho, old), ddiv(al, om));
             }
         }
-        go = state == ST_ACTIVE;
+        go = live && state == ST_ACTIVE;
         sc[0] = al.re, sc[1] = al.im, sc[2] = om.re, sc[3] = om.im, sc[4] = be.re, sc[5] = be.im;
         if (sb == 0) {
             BiRec &o = pr.recm[i];
             o.rr = rho.re, o.ri = rho.im, o.ar = al.re, o.ai = al.im, o.wr = om.re, o.wi = om.im;
             o.br = be.re, o.bi = be.im, o.rh2 = c.rh2, o.r2 = c.r2;
-            o.state = state, o.iters = c.iters, o.since_ru = c.since_ru, o.restart = 0;
+            o.state = state, o.iters = c.iters, o.since_ru = c.since_ru, o.restart = c.restart;
         }
     }
     __syncthreads();

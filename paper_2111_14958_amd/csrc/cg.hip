@@ -1330,8 +1330,9 @@ int cg_run(const wd_gauge *g, double m0, const void *src, void *sol, int nrhs, c
     // chunk after its fields converge.  Chunk boundaries only decide when the
     // host looks: the results are bitwise the same for any lengths.
     const bool adaptive = p.chunk == 0;
-    // every chunk of K either converges a field or spends K iterations of it
-    const int64_t budget = (int64_t)K * (p.max_iter / K + 2 * (p.max_iter / (K * 4) + 4));
+    // every chunk of K either converges a field or spends K iterations of it (fused
+    // BiCGSTAB: or restarts, at most one after each iteration)
+    const int64_t budget = (int64_t)K * (p.max_iter / K + 2 * (p.max_iter / (K * 4) + 4)) * (ls.bi_fused ? 2 : 1);
     const bool prof = g_prof_on.load() != 0 && !persistent && !bicg && !eo;
     int Kc = K;
     for (int64_t run = 0; run < budget && hsum[0] > 0; run += Kc) {
