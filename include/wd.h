@@ -133,8 +133,10 @@ int wd_unpack_spinor(const wd_gauge *g, int32_t prec, const void *in_dev, void *
  * (WD_F16N: half storage with per-site norms, FP32 arithmetic).  With
  * WD_PACKED the buffers are in the packed layout of `prec`; otherwise they are
  * canonical complex128: read and written directly in FP64 and FP32 where
- * Lx Ly <= 256 (and the launch shape is the default kind), else packed and
- * unpacked through stream-ordered temporary buffers, with the same results.  The gauge handle must hold the links in `prec`.
+ * Lx Ly <= 256 (and the launch shape is the default, or one set or tuned to
+ * plane blocks of one plane with hop order 5), else packed and unpacked through
+ * stream-ordered temporary buffers, with the same results.  The gauge handle must
+ * hold the links in `prec`.
  * in and out must not overlap.  Asynchronous on `stream`. */
 int wd_dslash(const wd_gauge *g, double m0, int32_t prec, const void *in_dev, void *out_dev,
               int32_t nrhs, uint32_t flags, void *stream);

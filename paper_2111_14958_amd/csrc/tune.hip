@@ -184,10 +184,11 @@ static void load_cache_locked() {
     fclose(f);
 }
 
-Shape shape_lookup(const ShapeKey &k) {
+Shape shape_lookup(const ShapeKey &k, bool *stored) {
     std::lock_guard<std::mutex> lk(g_mu);
     load_cache_locked();
     auto it = g_table.find(k);
+    if (stored) *stored = it != g_table.end();
     if (it != g_table.end()) return it->second.first;
     return default_shape(k);
 }

@@ -66,7 +66,8 @@ struct ShapeKey {
     int fam = FAM_DSLASH;
     bool operator<(const ShapeKey &o) const;
 };
-Shape shape_lookup(const ShapeKey &k);      // tuned entry or the default
+// the entry set, tuned or read from the cache file (*stored = true), or the default
+Shape shape_lookup(const ShapeKey &k, bool *stored = nullptr);
 void shape_store(const ShapeKey &k, const Shape &s);
 // shape_store, and append the entry to the cache file WD_TUNE_CACHE names (if any)
 void shape_store_persist(const ShapeKey &k, const Shape &s, double us);
