@@ -486,7 +486,11 @@ static int dslash_entry(const wd_gauge *g, double m0, int32_t prec, const void *
     if (flags & WD_PACKED) return launch_dslash(g, m0, prec, dag, in, out, nrhs, sh, st);
 
     // canonical complex128 in/out: directly, or pack, apply, unpack through temporaries
-    const bool direct = canonical_direct(g, prec, sh, stored);
+    // (which read all of the input before they write, so a shifted output that
+    // overlaps the input is right too; k_dslash_cn would race with itself)
+    const uintptr_t a0 = (uintptr_t)in, b0 = (uintptr_t)out, fb = (uintptr_t)g->V * 192 * nrhs;
+    const bool overlap = a0 < b0 + fb && b0 < a0 + fb;
+    const bool direct = !overlap && canonical_direct(g, prec, sh, stored);
     const size_t nb = spinor_bytes(prec, g->V, nrhs);
     if (noalloc) {
         // the two packed buffers, each at a 256-byte boundary, in the static scratch

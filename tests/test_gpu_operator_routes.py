@@ -77,3 +77,24 @@ def test_default_packed_fp32(dims, nrhs, planes, recon12):
         want = oracle.dirac(sitecheck.links_f32(U), sitecheck.links_f32(psi), dims, M0, -1, dagger=dag)
         sitecheck.assert_sites(got, want, psi, M0, sitecheck.F32_BOUND, "%s %d" % (dims, nrhs))
     g.close()
+
+
+@pytest.mark.parametrize("prec", [wd.F64, wd.F32], ids=["f64", "f32"])
+def test_overlapping_canonical_fields(prec):
+    """An output shifted by one field against the input takes the packed copies,
+    which read the whole input first; the fields are those of a call without overlap."""
+    import torch
+    dims, nrhs = (6, 9, 4, 7), 3
+    U, psi = _inputs(dims, nrhs, 5200)
+    g = wd.Gauge(dev(U), dims, -1)
+    x = dev(psi)
+    want = host(wd.dslash(g, M0, x, prec))
+    for shift in (1, -1):
+        buf = torch.zeros((nrhs + 1,) + tuple(x.shape[1:]), dtype=x.dtype, device="cuda")
+        src, dst = (buf[:nrhs], buf[1:]) if shift > 0 else (buf[1:], buf[:nrhs])
+        for call in (wd.dslash, wd.dslash_noalloc):
+            src.copy_(x)
+            say("overlapping canonical fields", prec, shift)
+            call(g, M0, src, prec, out=dst)
+            assert np.array_equal(host(dst).view(np.uint64), want.view(np.uint64))
+    g.close()
