@@ -57,10 +57,10 @@ namespace wd {
 // one rhs per thread (<= 168 VGPRs; left to the compiler some take more, which
 // allows 2).
 // FP64 site blocks with two hops in flight (order 3): held to two waves, so that
-// the second hop has its registers (phase B loads x_lo and the old q beside r
-// there).  Left to itself the compiler gives up the second hop for waves, which
-// these launches, short of blocks, do not have: whole solves 8 x 4 x 16 x 16 x 6
-// 4.80 -> 4.39 ms, 16 x 3 x 32 x 24 x 4 11.4 -> 10.9 ms, 4^4 2.13 -> 2.00 ms.
+// the second hop has its registers.  Left to itself the compiler gives up the
+// second hop for waves, which these launches, short of blocks, do not have: whole
+// solves 8 x 4 x 16 x 16 x 6 4.95 -> 4.62 ms, 6 x 8 x 8 x 8 x 3 3.34 -> 3.17, 4^4 2.14
+// -> 2.07, 16 x 3 x 32 x 24 x 4 12.8 -> 12.7 ms.
 template <int P, int NR, int ORD, bool XY>
 constexpr int phase_waves(bool most) {
     if (P == P64 && NR == 1 && ORD == 3 && !XY) return 2;
@@ -69,18 +69,18 @@ constexpr int phase_waves(bool most) {
 #define WD_PHASE_WAVES \
     __attribute__((amdgpu_waves_per_eu(phase_waves<P, NR, ORD, XY>(false), phase_waves<P, NR, ORD, XY>(true))))
 
-template <int P, int NR, int ORD, bool XY, bool R12 = false, int POL = 0, bool MP = false>
+template <int P, int NR, int ORD, bool XY, bool R12 = false, int POL = 0, bool MP = false, bool PAIR = XY>
 __global__ __launch_bounds__(MP ? 512 : 256) WD_PHASE_WAVES void k_phaseA(
     const Prob *__restrict__ probs, int nprob, int remap, int par, int first) {
     WD_KERNEL_PROLOGUE(KA)
-    phaseA_tile<P, NR, ORD, XY, R12, POL, true, MP>(pr, t_, par, first);
+    phaseA_tile<P, NR, ORD, XY, R12, POL, true, MP, PAIR>(pr, t_, par, first);
 }
 
-template <int P, int NR, int ORD, bool XY, bool R12 = false, int POL = 0, bool MP = false>
+template <int P, int NR, int ORD, bool XY, bool R12 = false, int POL = 0, bool MP = false, bool PAIR = XY>
 __global__ __launch_bounds__(MP ? 512 : 256) WD_PHASE_WAVES void k_phaseB(
     const Prob *__restrict__ probs, int nprob, int remap, int par, int last) {
     WD_KERNEL_PROLOGUE(KB)
-    phaseB_tile<P, NR, ORD, XY, R12, POL, true, MP>(pr, t_, par, last);
+    phaseB_tile<P, NR, ORD, XY, R12, POL, true, MP, PAIR>(pr, t_, par, last);
 }
 
 // direction-split phases A and B (phaseA_split_tile), four threads per site
@@ -226,13 +226,14 @@ void launch_eo_merge(const Prob *d, int64_t vf, int nrhs, void *sol, hipStream_t
 // iteration's phase A wrote (pr.sc2 for an odd K, else pr.sc) and its phase A
 // partials (slot 0 for an odd K, else slot 2) give the final records in pr.sc.
 // KS5 | FIN_TRAIL_BI: the trailing finish of a chunk of fused BiCGSTAB iterations.
-constexpr int FIN_AB = 0x100, FIN_TRAIL = 0x200, FIN_TRAIL_BI = 0x400;
+// FIN_SINGLE: x_lo is not updated in pairs (q stays in pr.q).
+constexpr int FIN_AB = 0x100, FIN_TRAIL = 0x200, FIN_TRAIL_BI = 0x400, FIN_SINGLE = 0x800;
 __global__ __launch_bounds__(1024) void k_finish(const Prob *__restrict__ probs, int nprob, int kind) {
     for (int j = 0; j < nprob; ++j) {
         const Prob &pr = probs[j];
         if (kind & FIN_TRAIL) {
             const int pk = (kind >> 12) & 1;
-            phaseAB_finish(pr, pk ? pr.sc2 : pr.sc, pr.sc, pk ? 0 : 2, pk ? 0 : 1);
+            phaseAB_finish(pr, pk ? pr.sc2 : pr.sc, pr.sc, pk ? 0 : 2, (kind & FIN_SINGLE) || pk ? 0 : 1);
             continue;
         }
         switch (kind) {
@@ -473,10 +474,26 @@ static void launch_split(const KindShape &k, hipStream_t st, const Prob *d, int 
     WD_TIMED_LAUNCH_LDS((k_phase_split<P, false, B>), gr, bl, k.lds, st, d, n, k.remap, par, edge);
 }
 
+// FP32 site blocks with x_lo updated in pairs (site_pair)
+template <bool B>
+static void launch_pair(const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int edge) {
+    const dim3 gr(k.grid), bl(k.block);
+    auto go = [&](auto a, auto b) {
+        if (B) WD_TIMED_LAUNCH(b, gr, bl, st, d, n, k.remap, par, edge);
+        else WD_TIMED_LAUNCH(a, gr, bl, st, d, n, k.remap, par, edge);
+    };
+    if (k.r12) go(k_phaseA<P32, 1, 3, false, true, 0, false, true>, k_phaseB<P32, 1, 3, false, true, 0, false, true>);
+    else go(k_phaseA<P32, 1, 3, false, false, 0, false, true>, k_phaseB<P32, 1, 3, false, false, 0, false, true>);
+}
+
 template <int P>
 static void launch_A(const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int first) {
     if (k.split) {
         launch_split<P, false>(k, st, d, n, par, first);
+        return;
+    }
+    if (k.pair && !k.xy) {
+        launch_pair<false>(k, st, d, n, par, first);
         return;
     }
     if (k.ordered == 5) launch_AB_o5<P, false>(k, st, d, n, par, first);
@@ -488,6 +505,10 @@ template <int P>
 static void launch_B(const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int last) {
     if (k.split) {
         launch_split<P, true>(k, st, d, n, par, last);
+        return;
+    }
+    if (k.pair && !k.xy) {
+        launch_pair<true>(k, st, d, n, par, last);
         return;
     }
     if (k.ordered == 5) launch_AB_o5<P, true>(k, st, d, n, par, last);
@@ -652,7 +673,8 @@ void launch_iterations(int inner, const LaunchSet &ls, hipStream_t st, const Pro
             if (ls.eo) launch_kind(KEB1, inner, ls, st, d, nprob, it & 1, 0);
             launch_kind(KB, inner, ls, st, d, nprob, it & 1, it == K - 1);
         }
-        hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, st, d, nprob, KB | FIN_AB | FIN_TRAIL | ((K & 1) << 12));
+        hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, st, d, nprob,
+                           KB | FIN_AB | FIN_TRAIL | ((K & 1) << 12) | (ls.eo || ls.k[KB].pair ? 0 : FIN_SINGLE));
         return;
     }
     for (int it = 0; it < K; ++it) {
@@ -803,7 +825,8 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
                               &sa, &sb, &sr};
     const int Vf = pr.vf;
     ls.eo = pr.eo;
-    const int policy = stream_policy(inner, iterated_bytes(inner, Vf, nrhs));
+    const size_t iterated = iterated_bytes(inner, Vf, nrhs);
+    const int policy = stream_policy(inner, iterated);
     for (int k = 0; k < NKIND; ++k) {
         KindShape &ks = ls.k[k];
         if (st[k]) {
@@ -907,6 +930,8 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
                     ks.lds = lds;
                 }
             }
+            if ((k == KA || k == KB) && !pr.eo)
+                ks.pair = ks.xy == 1 || (ks.xy == 0 && site_pair(inner, ks.ordered, ks.nr, iterated));
         } else {
             ks.block = 256;
             ks.nr = 1;
@@ -927,8 +952,9 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
     // phase A completes the previous iteration's finish: plane or site blocks
     // with phase A's reduction inside phase B, even-odd or not (not
     // z-marching).  WD_CG_UNFUSED=1 selects the iteration with finish launches
-    // instead (the same arithmetic; kept for comparisons).
-    ls.fused = ls.k[KA].xy != 2 && ls.k[KB].xy != 2 && !unfused_requested();
+    // instead (the same arithmetic; kept for comparisons), and so do shapes set
+    // for one phase only that pair x_lo's updates differently.
+    ls.fused = ls.k[KA].xy != 2 && ls.k[KB].xy != 2 && ls.k[KA].pair == ls.k[KB].pair && !unfused_requested();
 }
 
 // The persistent kernel runs phases A and B with one block shape, site blocks
@@ -960,6 +986,7 @@ void plan_persistent(LaunchSet &ls, Prob &pr, int64_t V, int nrhs, int inner, in
         ks.xy = 0;
         ks.planes = 1;
         ks.split = 0;
+        ks.pair = 0;
         ks.lds = 0;
         ks.r12 = cus && inner == WD_F32 && pr.U12 != nullptr;
         ks.nt = 0;
@@ -1032,7 +1059,7 @@ struct GraphKey {
     KindShape shp[NKIND];
     bool operator<(const GraphKey &o) const { return memcmp(this, &o, sizeof(*this)) < 0; }
 };
-static_assert(sizeof(KindShape) == 12 * sizeof(int), "KindShape must be plain ints (compared bytewise)");
+static_assert(sizeof(KindShape) == 13 * sizeof(int), "KindShape must be plain ints (compared bytewise)");
 
 struct GraphEntry {
     hipGraph_t graph = nullptr;
@@ -1165,9 +1192,10 @@ static int profiled_chunk(int inner, const LaunchSet &ls, hipStream_t st, const 
                 nc += it < d[i] - froze[i];
                 nq += it < d[i] && !(it == 0 && before[i].restart);   // phase A reads the old q
             }
-            // phase B's x_lo: in every iteration, or with the fused finish two
+            // phase B's x_lo: in every iteration, or paired (fused finish) two
             // iterations' updates in the launches of parity 1 (which read both q)
-            const double bx = !ls.fused ? 2.0 * SX : (it & 1) ? S + 2.0 * SX : it == K - 1 ? 2.0 * SX : 0.0;
+            const double bx = !ls.fused || !ls.k[KB].pair ? 2.0 * SX
+                              : (it & 1) ? S + 2.0 * SX : it == K - 1 ? 2.0 * SX : 0.0;
             const double bytes[3] = {G + nact * 2.0 * S + (ls.qrec ? nq * S : 0.0), G + nact * (3.0 * S + bx),
                                      nc * 3.0 * S};
             const int cnt[3] = {nact, nact, ls.qrec ? 0 : nc};

@@ -274,8 +274,9 @@ struct Fin {
     double sigma, alpha, rho_old, rho, beta;
     int state, iters, since_ru, pending_p, xq;
 };
-// xq: the record's xq if the field iterated
-__device__ __forceinline__ Fin cg_transition(const Prob &pr, const Scal &c0, double sigma, double rho, int xq) {
+// xq: the record's xq if the field iterated; max_iter, ru_every: the problem's
+__device__ __forceinline__ Fin cg_transition(const Scal &c0, double sigma, double rho, int xq, int max_iter,
+                                             int ru_every) {
     Fin f{c0.sigma, c0.alpha, c0.rho_old, c0.rho, c0.beta, c0.state, c0.iters, c0.since_ru, 0, c0.xq};
     if (c0.state != ST_ACTIVE) return f;
     f.xq = xq;
@@ -291,7 +292,7 @@ __device__ __forceinline__ Fin cg_transition(const Prob &pr, const Scal &c0, dou
     f.rho = rho;
     f.beta = rho / c0.rho;
     if (!(rho < 1e300)) f.state = ST_BREAKDOWN;   // NaN or Inf
-    else if (rho <= c0.stop2 || f.iters >= pr.max_iter || (pr.ru_every > 0 && f.since_ru >= pr.ru_every))
+    else if (rho <= c0.stop2 || f.iters >= max_iter || (ru_every > 0 && f.since_ru >= ru_every))
         f.state = ST_FROZEN;                        // wants a reliable update
     else f.pending_p = 1;
     return f;
@@ -366,20 +367,22 @@ template <int NR> struct FinShared {
     double sig[NR], rho[NR], beta[NR];
     int act[NR], restart[NR], oldq[NR];   // oldq: the buffer of the old q (0: pr.q, 1: pr.p)
 };
-template <int NR> struct FusedFinish {
+// PAIR: q in two buffers (see phaseA_tile).
+template <int NR, bool PAIR> struct FusedFinish {
     const Prob &pr;
     FinShared<NR> &sh;
     const int rhs0, par;
     const bool fused, fin;   // uniform over the launch
     const Scal *sin;
     const int xqn;           // xq of a field that iterated before this launch (parity par ^ 1)
+    int max_iter, ru_every;
     unsigned act0;           // fields that iterate before this launch's finish (uniform over the block)
     Scal c0[NR];
     double as[NR][4], ar[NR][4];
 
     __device__ __forceinline__ FusedFinish(const Prob &p, FinShared<NR> &f, int r0, bool on, int pa, int first)
         : pr(p), sh(f), rhs0(r0), par(pa), fused(on && pa >= 0), fin(on && pa >= 0 && !first),
-          sin(on && pa > 0 ? p.sc2 : p.sc), xqn(pa ? 2 : 1) {
+          sin(on && pa > 0 ? p.sc2 : p.sc), xqn(!PAIR ? 0 : pa ? 2 : 1) {
         act0 = rhs_mask<NR>(pr, sin, rhs0, ST_ACTIVE);
     }
     __device__ __forceinline__ void begin() {
@@ -397,9 +400,13 @@ template <int NR> struct FusedFinish {
                 c0[j].since_ru = m.since_ru;
                 c0[j].beta = m.beta;
                 c0[j].restart = m.restart;
-                c0[j].xq = m.xq;
+                if constexpr (PAIR) c0[j].xq = m.xq;
             }
         }
+        // here, not in the chain of the decision
+        max_iter = pr.max_iter;
+        ru_every = pr.ru_every;
+        asm volatile("" : "+s"(max_iter), "+s"(ru_every));
         if (fin && act0) {
             col_issue<NR>(pr, rhs0, act0, as, par ? 0 : 2, pr.nsb[KA]);
             col_issue<NR>(pr, rhs0, act0, ar, 1, pr.nsb[KB]);
@@ -419,16 +426,17 @@ template <int NR> struct FusedFinish {
             for (int j = 0; j < NR; ++j) {
                 const bool live = act0 >> j & 1;
                 if (fin) {
-                    const Fin f = cg_transition(pr, c0[j], live ? sh.sig[j] : 0.0, live ? sh.rho[j] : 0.0, xqn);
+                    const double sg = sh.sig[j], rh = sh.rho[j];
+                    const Fin f = cg_transition(c0[j], live ? sg : 0.0, live ? rh : 0.0, xqn, max_iter, ru_every);
                     sh.act[j] = live && f.state == ST_ACTIVE;
                     sh.beta[j] = f.beta;
                     sh.restart[j] = 0;
-                    sh.oldq[j] = par ^ 1;
+                    if constexpr (PAIR) sh.oldq[j] = par ^ 1;
                 } else {
                     sh.act[j] = live;
                     sh.beta[j] = c0[j].beta;
                     sh.restart[j] = c0[j].restart;
-                    sh.oldq[j] = c0[j].xq & 1;
+                    if constexpr (PAIR) sh.oldq[j] = c0[j].xq & 1;
                 }
             }
         __syncthreads();
@@ -443,11 +451,11 @@ template <int NR> struct FusedFinish {
     }
     __device__ __forceinline__ double beta(int j) const { return fused ? sh.beta[j] : pr.sc[rhs0 + j].beta; }
     __device__ __forceinline__ void *oldq(int j) const {   // the same in every lane: a scalar choice
-        return fused && __builtin_amdgcn_readfirstlane(sh.oldq[j]) ? pr.p : pr.q;
+        return PAIR && fused && __builtin_amdgcn_readfirstlane(sh.oldq[j]) ? pr.p : pr.q;
     }
     // slot of phase A's partials, buffer of the new q
     __device__ __forceinline__ int slot() const { return fused && par ? 2 : 0; }
-    __device__ __forceinline__ void *newq() const { return fused && par ? pr.p : pr.q; }
+    __device__ __forceinline__ void *newq() const { return PAIR && fused && par ? pr.p : pr.q; }
     // the group's records after the finish (or copied unchanged in the chunk's
     // first iteration), from the complete records read again: by site block 0
     __device__ __forceinline__ void store(int sb) {
@@ -460,7 +468,8 @@ template <int NR> struct FusedFinish {
                     if (fin) {
                         const bool live = act0 >> j & 1;
                         store_fin(sout[rhs0 + j], full,
-                                  cg_transition(pr, full, live ? sh.sig[j] : 0.0, live ? sh.rho[j] : 0.0, xqn));
+                                  cg_transition(full, live ? sh.sig[j] : 0.0, live ? sh.rho[j] : 0.0, xqn, max_iter,
+                                                ru_every));
                     } else {
                         sout[rhs0 + j] = full;
                     }
@@ -494,12 +503,12 @@ template <int NR> struct FusedFinish {
 // records are final already (the reliable update or the trailing finish of the
 // chunk before wrote them) and are copied unchanged.  Partials go to slot 0
 // (par 0) or 2 (par 1).
-// With the fused finish q alternates between two buffers, pr.q (par 0) and
+// PAIR: with the fused finish q alternates between two buffers, pr.q (par 0) and
 // pr.p (par 1), so that phase B can add two iterations' alpha q to x_lo in one
 // pass (see phaseB_tile): the old q is read from the other buffer (in the
 // chunk's first iteration, from the one the field's record names).
 template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, int POL = 0, bool QR = false,
-          bool MP = false>
+          bool MP = false, bool PAIR = XY>
 __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1, int first = 0) {
     typedef typename real_of<P>::type R;
     typedef typename LdsSpinor<P>::word W;
@@ -508,7 +517,7 @@ __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1,
     int sb, grp, s;
     stencil_tile<XY, MP>(pr, KA, t, sb, grp, s);
     const int rhs0 = grp * NR;
-    FusedFinish<NR> ff(pr, fs, rhs0, QR, par, first);
+    FusedFinish<NR, PAIR> ff(pr, fs, rhs0, QR, par, first);
     const unsigned act0 = ff.act0;
     double part[NR];
 #pragma unroll
@@ -630,7 +639,7 @@ __device__ __forceinline__ void fa_reduce(const Prob &pr, int rhs0, unsigned act
 // par >= 0 (with FA; the fused finish, see phaseA_tile): the records are those
 // the phase-A launch of iteration parity par wrote (pr.sc2 for par 0, pr.sc for
 // 1) and phase A's partials are in slot 0 (par 0) or 2 (par 1).
-// x_lo is not needed inside the iteration, so with the fused finish it is
+// PAIR: x_lo is not needed inside the iteration, so with the fused finish it is
 // updated in every second one: the launch of parity 1 adds the iteration
 // before's alpha q (the other q buffer, the record's alpha) and then its own,
 // in the order and with the roundings of two single updates, so the solution
@@ -642,9 +651,11 @@ __device__ __forceinline__ void fa_reduce(const Prob &pr, int rhs0, unsigned act
 // 33.2 ms; a single 8^4 field, bound by latency, 2.08 -> 2.10 ms.  last = 1
 // (the chunk's last iteration): parity 0 adds its own alpha q at once.  A
 // field that freezes after a parity-0 iteration keeps its pending alpha q (xq
-// bit 1) for R1.
+// bit 1) for R1.  Plane blocks are paired; site blocks in FP32 while the fields
+// (one q more) stay in the L2s (site_pair), and not in FP64 and FP16N, where the
+// single update with q held in registers is the faster one.
 template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, int POL = 0, bool FA = false,
-          bool MP = false>
+          bool MP = false, bool PAIR = XY>
 __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1, int last = 0) {
     typedef typename real_of<P>::type R;
     constexpr int XP = XPrec<P>::value;
@@ -663,8 +674,8 @@ __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1,
     for (int j = 0; j < NR; ++j) part[j] = 0.0;
     const Geom g = pr.g;
     const int np = MP ? g.S[2] * xy_kp(pr.sorder[KB]) : g.S[2];   // sites staged in LDS
-    FieldPtr fq{par > 0 ? pr.p : pr.q, g.V, pr.nrhs}, fr{pr.r, g.V, pr.nrhs}, fx{pr.x_lo, g.V, pr.nrhs};
-    const bool xup = par != 0 || last;   // this launch updates x_lo
+    FieldPtr fq{PAIR && par > 0 ? pr.p : pr.q, g.V, pr.nrhs}, fr{pr.r, g.V, pr.nrhs}, fx{pr.x_lo, g.V, pr.nrhs};
+    const bool xup = !PAIR || par != 0 || last;   // this launch updates x_lo
     if constexpr (FA) {
         if (act) {   // uniform over the block
             double a[NR][4];
@@ -706,14 +717,13 @@ __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1,
                 for (int k = 0; k < 12; ++k) n += (double)norm2(r[k]);
                 part[j] = n;
                 if (!xup) continue;
-                // issued once r is done with (no instruction): three more
+                // paired: issued once r is done with (no instruction): three more
                 // spinors loaded ahead of it would cost phase B a wave per SIMD
-                // (FP64 site blocks have waves to spare, see phase_waves)
                 int sx = s;
-                if constexpr (XY || P != P64) asm volatile("" : "+v"(sx) : "v"(n));
+                if constexpr (PAIR) asm volatile("" : "+v"(sx) : "v"(n));
                 cx<RX> x[12];
                 Spinor<XP>::template load<POL>(fx, rhs0 + j, sx, x);
-                if (par > 0) {   // the iteration before's update first
+                if (PAIR && par > 0) {   // the iteration before's update first
                     const FieldPtr fo{pr.q, g.V, pr.nrhs};
                     const RX ao = (RX)sc[rhs0 + j].alpha;
                     cx<R> qo[12];
@@ -721,12 +731,13 @@ __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1,
 #pragma unroll
                     for (int k = 0; k < 12; ++k) x[k] = {x[k].re + ao * (RX)qo[k].re, x[k].im + ao * (RX)qo[k].im};
                 }
-                // q read again (from LDS, or a line this thread has just read), so
-                // that it is not held meanwhile
-                int tx = XY ? (int)threadIdx.x : sx;
-                if constexpr (XY || P != P64) asm volatile("" : "+v"(tx) : "v"(x[0].re), "v"(x[11].im));
-                if constexpr (XY) LdsSpinor<P>::get(xy, np, j, tx, q);
-                else Spinor<P>::load(fq, rhs0 + j, tx, q);
+                if constexpr (PAIR) {   // q read again (from LDS, or a line this thread has just
+                                        // read), so that it is not held meanwhile
+                    int tx = XY ? (int)threadIdx.x : sx;
+                    asm volatile("" : "+v"(tx) : "v"(x[0].re), "v"(x[11].im));
+                    if constexpr (XY) LdsSpinor<P>::get(xy, np, j, tx, q);
+                    else Spinor<P>::load(fq, rhs0 + j, tx, q);
+                }
                 const RX ax = (RX)al;
 #pragma unroll
                 for (int k = 0; k < 12; ++k) x[k] = {x[k].re + ax * (RX)q[k].re, x[k].im + ax * (RX)q[k].im};
@@ -812,11 +823,11 @@ __device__ __forceinline__ void phaseAB_finish(const Prob &pr, const Scal *sin, 
     Scal c0;
     if (i < pr.nrhs) c0 = sin[i];
     if (!__syncthreads_or(i < pr.nrhs && c0.state == ST_ACTIVE)) {   // nothing to sum
-        if (i < pr.nrhs) store_fin(sout[i], c0, cg_transition(pr, c0, 0.0, 0.0, xq));
+        if (i < pr.nrhs) store_fin(sout[i], c0, cg_transition(c0, 0.0, 0.0, xq, pr.max_iter, pr.ru_every));
         return;
     }
     sum_ab(pr, sa, sbb, aslot);
-    if (i < pr.nrhs) store_fin(sout[i], c0, cg_transition(pr, c0, sa[i], sbb[i], xq));
+    if (i < pr.nrhs) store_fin(sout[i], c0, cg_transition(c0, sa[i], sbb[i], xq, pr.max_iter, pr.ru_every));
 }
 __device__ __forceinline__ void phaseAB_finish(const Prob &pr) { phaseAB_finish(pr, pr.sc, pr.sc, 0, 0); }
 
@@ -851,7 +862,7 @@ __device__ __forceinline__ void phaseA_split_tile(const Prob &pr, int t, int par
     __shared__ FinShared<1> fs;
     int sb, rhs, d, i, s;
     split_tile(pr, KA, t, sb, rhs, d, i, s);
-    FusedFinish<1> ff(pr, fs, rhs, true, par, first);
+    FusedFinish<1, true> ff(pr, fs, rhs, true, par, first);
     const Geom g = pr.g;
     const int np = g.S[2];
     W *xy = (W *)lds;

@@ -20,6 +20,7 @@ struct KindShape {
     int nt = 0;        // phases A and B: cache policy of the streaming accesses (stream_policy)
     int planes = 1;    // phases A and B, plane-blocked: z-adjacent xy-planes per block
     int split = 0;     // phases A and B, plane-blocked: four groups of threads per plane, one per direction
+    int pair = 0;      // phases A and B: x_lo updated once per pair of iterations (phaseB_tile)
 };
 struct LaunchSet {
     KindShape k[NKIND];
@@ -48,6 +49,16 @@ struct WsLayout {
     size_t total;
 };
 
+// Site-blocked phases A and B that update x_lo in pairs: FP32 with two hops in
+// flight and one rhs per thread, while r, q in two buffers and x_lo (bytes) fit
+// three quarters of the eight 4 MB L2s.  Whole solves, single against paired: 8 x
+// 4 x 16 x 16 x 6 (18.9 MB) 3.44 -> 3.33 ms, 6 x 8 x 8 x 8 x 3 2.64 -> 2.59; but 7 x 7
+// x 14 x 14 x 8 (29.5 MB) 4.36 -> 4.43, 4 x 14 x 12 x 14 x 12 (43 MB) 4.79 -> 4.87, 16
+// x 3 x 32 x 24 x 4 (57 MB) 6.54 -> 6.77 ms.  FP64 at these sizes 4.62 -> 4.93, 3.17
+// -> 3.18, 7.97 -> 8.13, 8.58 -> 8.77, 12.69 -> 12.81; FP16N within 1 % of each other.
+inline int site_pair(int prec, int ordered, int nr, size_t bytes) {
+    return prec == WD_F32 && ordered == 3 && nr == 1 && bytes <= (size_t)24 << 20;
+}
 // LDS bytes of a direction-split block: the staged plane of np sites and the
 // sums' two buffers (24 reals per site each)
 inline int split_lds_bytes(int prec, int np) { return 3 * np * (prec == WD_F64 ? 192 : 96); }

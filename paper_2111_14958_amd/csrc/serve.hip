@@ -161,7 +161,11 @@ static LaunchSet server_launch(int inner, int eo, int xy, const int grid[NKIND])
         ls.k[k].nr = 1;
         ls.k[k].remap = stencil ? 1 : 0;
         ls.k[k].grid = grid[k];
-        if (k == KA || k == KB) ls.k[k].ordered = 3;
+        if (k == KA || k == KB) {
+            ls.k[k].ordered = 3;
+            ls.k[k].pair = !eo && (xy || inner == WD_F32);   // FP32 site blocks: for every request, so
+                                                             // that slots keep the buffer of their q
+        }
         if (xy && (k == KA || k == KB)) {
             ls.k[k].xy = 1;
             ls.k[k].ordered = 5;
