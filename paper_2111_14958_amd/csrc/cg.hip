@@ -792,9 +792,11 @@ static size_t iterated_bytes(int inner, int64_t Vf, int nrhs) {
 // Cache policy (see ld) of the phases' streaming accesses, by whether the fields
 // an iteration touches (r, q in two buffers, x_lo) fit the 256 MB MALL.  They do:
 // plain (0), but device-scope accesses (2) in FP64 from 128 MB on, which leave
-// the L2 to the gathered field: whole solves 12^4 x 12 plain 12.55, device-scope
-// 12.28 ms (nontemporal 13.3); 14^4 x 2, of which the L2s hold a good part, 5.62
-// against 5.85 ms.  In FP32 device-scope accesses are not kept: 14^4 x 16 15.7 ->
+// the L2 to the gathered field: whole solves, plain against device-scope, 12^4 x 12
+// 12.55 -> 12.28 ms (nontemporal 13.3), 8 x 8 x 14 x 28 x 10 21.7 -> 20.9, 16^4 x 4
+// 16.3 -> 15.8, 14^4 x 8 19.6 -> 19.2, 12 x 12 x 16 x 20 x 5 15.6 -> 15.3, 14 x 10 x
+// 12 x 24 x 5 13.78 -> 13.72, and by 1 to 2 % on four lattices more in the window;
+// 14^4 x 2, of which the L2s hold a good part, 5.62 -> 5.85 ms.  In FP32 device-scope accesses are not kept: 14^4 x 16 15.7 ->
 // 15.5 ms, but 14 x 10 x 12 x 24 x 5 6.54 -> 7.02, 8 x 8 x 14 x 28 x 10 9.8 -> 10.4
 // ms.  They do not fit: FP64 nontemporal (1), 14^4 x 16 plain 33.8, device-scope
 // 34.0, nontemporal 30.8 ms; FP32 and FP16N nontemporal loads with device-scope
@@ -887,14 +889,18 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
             // even-odd: the phases' half-lattice hops on half-plane blocks (the
             // Lx Ly / 2 sites of one parity on an xy-plane, 64..256 of them),
             // one rhs per thread, hop order 5.  FP16N, whose coding keeps the
-            // phases bound by issue: not between one and four blocks per compute
-            // unit.  Whole solves, site against half-plane blocks: 16^3 x 32 x 1
-            // (512 blocks) 4.54 -> 5.28 ms, 16^4 x 2 3.87 -> 4.33 ms; 14^4 x 1
-            // (196) 3.54 -> 3.28, 16^3 x 32 x 4 (2048) 9.25 -> 9.08 ms
+            // phases bound by issue: site blocks from more than one to two
+            // half-plane blocks per compute unit, whatever the phases' shapes ask
+            // for.  Whole solves, site against half-plane blocks (of 128): 16 x 16 x
+            // 8 x 9 x 4 (288 blocks) 3.97 -> 4.42, 16 x 16 x 8 x 8 x 6 (384) 3.85 ->
+            // 4.37, 16^3 x 32 x 1 (512) 4.98 -> 5.76 ms; but 16^4 x 1 (256) 3.68 ->
+            // 3.62, 16 x 16 x 12 x 12 x 4 (576) 5.20 -> 4.97, 16 x 16 x 10 x 16 x 4
+            // (640) 5.38 -> 5.09, 16^4 x 3 (768) 5.42 -> 5.23, 16^3 x 32 x 4 (2048)
+            // 9.25 -> 9.08 ms
             if (pr.eo && (k == KA || k == KB || k == KEA1 || k == KEB1)) {
                 const int nh = np / 2;
                 const int64_t hb = (int64_t)V / np * nrhs;
-                const bool idle = inner == WD_F16N && hb > 256 && hb < 1024;
+                const bool idle = inner == WD_F16N && hb > 256 && hb <= 512;
                 ks.xy = st[k]->xylds && nh >= 64 && nh <= 256 && !idle ? 1 : 0;
                 ks.order = 0;
                 if (ks.xy) {
