@@ -130,9 +130,13 @@ Shape default_shape(const ShapeKey &k) {
         if (s.xylds) s.ordered = 5;
         if (s.xylds && prec != WD_F64 && cg_two_planes(k.L, nrhs)) {
             s.planes = 2;
-            // wider strips with few fields (16^3 x 32, 2 fields, FP32: 8.0 -> 7.6
-            // ms; 12 fields, FP16N: 28.8 -> 29.6 ms)
-            s.strip = nrhs <= 4 ? 8 : 4;
+            // wider strips with few fields, and with three or four where t is
+            // long against z.  Whole solves, strips of 4 against 8: 16^3 x 32 FP32
+            // 1 / 2 / 3 / 4 / 6 / 12 fields 5.68 -> 5.59, 9.18 -> 8.77, 12.71 -> 12.52,
+            // 16.02 -> 15.94, 21.8 -> 22.0, 48.8 -> 49.4 ms (FP16N -2.5, -1.1, -0.6,
+            // -0.6, 0, +0.6 %), 16 x 16 x 8 x 32 x 4 9.29 -> 9.03; but 16^4 x 4 8.00 ->
+            // 8.47, 16^3 x 24 x 4 11.76 -> 11.88 ms
+            s.strip = nrhs <= 2 || (nrhs <= 4 && k.L[3] >= 2 * k.L[2]) ? 8 : 4;
         }
     }
     return s;
