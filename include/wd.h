@@ -233,7 +233,9 @@ typedef struct {
  *   normal equations of the Schur complement Dhat = A - D_eo A^-1 D_oe on the
  *   even sites, and the odd half of x follows from the even half.  The test
  *   |b_e - Dhat x_e| <= tol |eta| is the full system's true residual.  CG
- *   (WD_METHOD_CGNE) only, not with the persistent kernel; Lx must be even.
+ *   (WD_METHOD_CGNE) only, not with the persistent kernel; Lx must be even.  With
+ *   an odd Ly, Lz or Lt the wrap-around joins sites of one parity and there is no
+ *   such splitting: the solve then runs without preconditioning.
  *   The paper asks for operator forms better suited to the Dirac operator
  *   (Conclusions) without describing one; this is the textbook elimination. */
 #define WD_PRECOND_NONE 0

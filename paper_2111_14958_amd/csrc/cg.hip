@@ -1009,7 +1009,7 @@ void fill_prob(Prob &pr, const wd_gauge *g, double m0, int nrhs, const wd_cg_par
                char *ws, const WsLayout &L) {
     pr.g = make_geom(g);
     pr.diag = 4.0 + m0;
-    pr.eo = p.precondition == WD_PRECOND_EO ? 1 : 0;
+    pr.eo = even_odd(p, g->dims);
     pr.vf = pr.eo ? (int)(g->V / 2) : (int)g->V;
     pr.eo_c = 0.25 / pr.diag;
     pr.tol2 = p.tol * p.tol;
@@ -1245,7 +1245,7 @@ int cg_run(const wd_gauge *g, double m0, const void *src, void *sol, int nrhs, c
            void *ws, size_t ws_bytes, wd_cg_report *reps, hipStream_t st) {
     const auto t_start = std::chrono::steady_clock::now();
     const int64_t V = g->V;
-    const int eo = p.precondition == WD_PRECOND_EO ? 1 : 0;
+    const int eo = even_odd(p, g->dims);
     const WsLayout L = ws_layout(V, nrhs, p.inner, p.method, eo);
     WD_CHECK(ws_bytes >= L.least, WD_ENOMEM, "workspace of %zu bytes, %zu needed", ws_bytes, L.least);
     char *w = (char *)ws;
@@ -1470,7 +1470,7 @@ size_t wd_cg_workspace_bytes(const wd_gauge *g, int32_t nrhs, const wd_cg_params
     if (!g || !p || nrhs < 1 || nrhs > MAX_RHS || p->inner < 0 || p->inner > 2) return 0;
     if (p->method != METHOD_CGNE && p->method != METHOD_BICGSTAB) return 0;
     if (p->precondition != WD_PRECOND_NONE && p->precondition != WD_PRECOND_EO) return 0;
-    return ws_layout(g->V, nrhs, p->inner, p->method, p->precondition == WD_PRECOND_EO).total;
+    return ws_layout(g->V, nrhs, p->inner, p->method, even_odd(*p, g->dims)).total;
 }
 
 int wd_cg_solve_batch(const wd_gauge *g, double m0, const void *src, void *sol, int32_t nrhs,

@@ -63,6 +63,13 @@ inline int site_pair(int prec, int ordered, int nr, size_t bytes) {
 // sums' two buffers (24 reals per site each)
 inline int split_lds_bytes(int prec, int np) { return 3 * np * (prec == WD_F64 ? 192 : 96); }
 
+// Does a solve run even-odd preconditioned?  Where it is asked for and every extent
+// is even; with an odd one the wrap joins sites of one parity, so there is no
+// even-odd splitting and the solve runs without.
+inline int even_odd(const wd_cg_params &p, const int *dims) {
+    return p.precondition == WD_PRECOND_EO && !((dims[0] | dims[1] | dims[2] | dims[3]) & 1);
+}
+
 WsLayout ws_layout(int64_t V, int nrhs, int inner, int method, int eo = 0);
 void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr);
 void plan_persistent(LaunchSet &ls, Prob &pr, int64_t V, int nrhs, int inner, int max_cus = 0);

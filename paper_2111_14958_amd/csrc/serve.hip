@@ -390,7 +390,7 @@ static void scheduler(wd_server *s) {
                 const SlotLayout lay = slot_layout((int64_t)it->req.dims[0] * it->req.dims[1] *
                                                        it->req.dims[2] * it->req.dims[3],
                                                    it->req.nrhs, it->req.params.inner,
-                                                   it->req.params.precondition == WD_PRECOND_EO);
+                                                   even_odd(it->req.params, it->req.dims));
                 size_t off = 0;
                 if (nslots < s->cfg.max_slots && s->arena.alloc(lay.total, &off)) {
                     Slot sl;
@@ -511,7 +511,7 @@ extern "C" {
 size_t wd_serve_footprint(const wd_request *req) {
     if (check_request(req) != WD_OK) return 0;
     const int64_t V = (int64_t)req->dims[0] * req->dims[1] * req->dims[2] * req->dims[3];
-    return al256s(slot_layout(V, req->nrhs, req->params.inner, req->params.precondition == WD_PRECOND_EO).total);
+    return al256s(slot_layout(V, req->nrhs, req->params.inner, even_odd(req->params, req->dims)).total);
 }
 
 int wd_serve_create(const wd_serve_config *cfg, wd_server **out) {
