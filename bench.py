@@ -202,10 +202,11 @@ def main():
         mp = bool(xy) and nr == 1 and sh["hop_order"] == 5 and sh.get("xy_planes", 1) > 1
         # cache policy of the streams: r, q twice and x_lo against the 256 MB MALL
         policy = (0 if 4 * 96 * V * nrhs <= 256 << 20 else 3) if xy and nr == 1 and sh["hop_order"] == 5 else 0
-        kernel_symbol = "wd::k_%s<1, %d, %d, %s, true, %d, %s>" % (
+        # x_lo updated in pairs: plane blocks, and small site blocks
+        pair = bool(xy) or (sh["hop_order"] == 3 and nr == 1 and 4 * 96 * V * nrhs <= 24 << 20)
+        kernel_symbol = "wd::k_%s<1, %d, %d, %s, true, %d, %s, %s>" % (
             dom_name[3:], nr, sh["hop_order"] if sh["hop_order"] in (3, 5) else 1, "true" if xy else "false",
-            policy,
-            "true" if mp else "false")
+            policy, "true" if mp else "false", "true" if pair else "false")
     else:
         kernel_symbol = dom_name
     traffic, traffic_note = pmc_traffic() if dom_name == "cg_phaseB" else (None, "not measured")

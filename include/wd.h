@@ -300,7 +300,11 @@ typedef struct {
                              one plane);
                              group_major = 1: tiles are ordered rhs-group-major
                              instead of site-block-major; xy_lds = 1: one xy-plane
-                             per block with the x/y neighbours in LDS; occ > 0: at
+                             per block with the x/y neighbours in LDS (CG phases A
+                             and B with hop order 5 and one plane per block: four
+                             threads per site, one per direction, in launches of at
+                             most 256 blocks, 512 of 64 sites; even-odd FP16N
+                             solves: site blocks between 257 and 512 blocks); occ > 0: at
                              most occ plane blocks per compute unit (operator);
                              z_march = 1 (with xy_lds = 1; CG phases A and B in
                              FP32/FP16N storage): a block walks a column of

@@ -13,7 +13,7 @@
 // <a, b> = sum conj(a) b.  A reliable update restarts with r_hat = r = eta - D x;
 // a (near) breakdown |<r_hat, r>| <= 1e-6 |r_hat| |r| restarts with r_hat = r.
 //
-// Fused iteration (BiFused records; the default): four launches, every
+// Fused iteration (BiRec records; the default): four launches, every
 // reduction completed by the launch that needs it, instead of five stages and
 // three one-block finishes:
 //   F2  completes |r|^2: counters, state, tests;  v = D p,  <r_hat, v>
@@ -30,6 +30,10 @@
 // finish closes the last iteration into the final records, and the next chunk's
 // S1 sets p = r_hat = r, as it does after a reliable update: the iterates are the
 // same wherever chunks end.
+// (rho does not see the rounding of the stored r.  Against <r_hat, r> over 1056
+// fields of 4^4 to 12^4 stopped at 1e-10, mean change in FP32 and FP16N: iterations
+// 0.03 +- 0.04 and -0.02 +- 0.06, error against an FP64 solution at 1e-14 -4.5 +-
+// 2.0 % and -0.7 +- 1.4 %; in FP64 neither changed on 180 fields.)
 // The five-stage iteration remains for workspaces without the fused one's
 // records.  12^4 x 4 FP32, where launches and latency bound: a solve 4.36 -> 3.61
 // ms, 3.33 ms with the last chunk cut to the estimated need.

@@ -12,9 +12,11 @@
 // (phase C, p = r + beta p, with phase A reading p, remains for the z-marching
 // phase-A kernel).  Every scalar lives in device memory, one record per
 // right-hand side.  Phase B's blocks complete phase A's reduction themselves,
-// and a one-block launch after phase B sums the per-block partials of both in
-// a fixed order and updates the scalars, so nothing returns to the host inside
-// an iteration and reductions are bitwise reproducible.
+// and the next iteration's phase A the finish of both (FusedFinish; a one-block
+// launch closes a chunk's last iteration, or every one with WD_CG_UNFUSED=1, a
+// z-marching phase or phases that pair x_lo's updates differently).  Partials
+// are summed in a fixed order, so nothing returns to the host inside an
+// iteration and reductions are bitwise reproducible.
 //
 // Mixed precision: q, r, x_lo (and p) are stored in the inner precision (FP16N
 // keeps x_lo in FP32).  A reliable update (R1, R2) accumulates x64 += x_lo and
@@ -367,15 +369,18 @@ template <int NR> struct FinShared {
     double sig[NR], rho[NR], beta[NR];
     int act[NR], restart[NR], oldq[NR];   // oldq: the buffer of the old q (0: pr.q, 1: pr.p)
 };
-// PAIR: q in two buffers (see phaseA_tile).
-template <int NR, bool PAIR> struct FusedFinish {
+// PAIR: q in two buffers (see phaseA_tile).  EARLY: what the decision reads is
+// loaded before it, not in its chain of branches (site blocks, where nothing
+// covers it: a 4^4 field in FP32 1.67 -> 1.64 ms; plane and half-plane blocks are
+// 0.2 to 0.5 % faster without).
+template <int NR, bool PAIR, bool EARLY> struct FusedFinish {
     const Prob &pr;
     FinShared<NR> &sh;
     const int rhs0, par;
     const bool fused, fin;   // uniform over the launch
     const Scal *sin;
     const int xqn;           // xq of a field that iterated before this launch (parity par ^ 1)
-    int max_iter, ru_every;
+    int max_iter, ru_every;  // EARLY
     unsigned act0;           // fields that iterate before this launch's finish (uniform over the block)
     Scal c0[NR];
     double as[NR][4], ar[NR][4];
@@ -403,10 +408,11 @@ template <int NR, bool PAIR> struct FusedFinish {
                 if constexpr (PAIR) c0[j].xq = m.xq;
             }
         }
-        // here, not in the chain of the decision
-        max_iter = pr.max_iter;
-        ru_every = pr.ru_every;
-        asm volatile("" : "+s"(max_iter), "+s"(ru_every));
+        if constexpr (EARLY) {
+            max_iter = pr.max_iter;
+            ru_every = pr.ru_every;
+            asm volatile("" : "+s"(max_iter), "+s"(ru_every));
+        }
         if (fin && act0) {
             col_issue<NR>(pr, rhs0, act0, as, par ? 0 : 2, pr.nsb[KA]);
             col_issue<NR>(pr, rhs0, act0, ar, 1, pr.nsb[KB]);
@@ -418,6 +424,13 @@ template <int NR, bool PAIR> struct FusedFinish {
             col_reduce<NR>(pr, rhs0, act0, ar, sh.rho, 1, pr.nsb[KB]);
         }
     }
+    __device__ __forceinline__ Fin transition(const Scal &c, int j, bool live) const {
+        if constexpr (EARLY) {
+            const double sg = sh.sig[j], rh = sh.rho[j];
+            return cg_transition(c, live ? sg : 0.0, live ? rh : 0.0, xqn, max_iter, ru_every);
+        } else
+            return cg_transition(c, live ? sh.sig[j] : 0.0, live ? sh.rho[j] : 0.0, xqn, pr.max_iter, pr.ru_every);
+    }
     // thread 0 applies the finish and shares the decision through LDS (one barrier)
     __device__ __forceinline__ unsigned decide() {
         if (!fused) return act0;
@@ -426,8 +439,7 @@ template <int NR, bool PAIR> struct FusedFinish {
             for (int j = 0; j < NR; ++j) {
                 const bool live = act0 >> j & 1;
                 if (fin) {
-                    const double sg = sh.sig[j], rh = sh.rho[j];
-                    const Fin f = cg_transition(c0[j], live ? sg : 0.0, live ? rh : 0.0, xqn, max_iter, ru_every);
+                    const Fin f = transition(c0[j], j, live);
                     sh.act[j] = live && f.state == ST_ACTIVE;
                     sh.beta[j] = f.beta;
                     sh.restart[j] = 0;
@@ -467,9 +479,7 @@ template <int NR, bool PAIR> struct FusedFinish {
                     const Scal full = sin[rhs0 + j];
                     if (fin) {
                         const bool live = act0 >> j & 1;
-                        store_fin(sout[rhs0 + j], full,
-                                  cg_transition(full, live ? sh.sig[j] : 0.0, live ? sh.rho[j] : 0.0, xqn, max_iter,
-                                                ru_every));
+                        store_fin(sout[rhs0 + j], full, transition(full, j, live));
                     } else {
                         sout[rhs0 + j] = full;
                     }
@@ -517,7 +527,7 @@ __device__ __forceinline__ void phaseA_tile(const Prob &pr, int t, int par = -1,
     int sb, grp, s;
     stencil_tile<XY, MP>(pr, KA, t, sb, grp, s);
     const int rhs0 = grp * NR;
-    FusedFinish<NR, PAIR> ff(pr, fs, rhs0, QR, par, first);
+    FusedFinish<NR, PAIR, !XY> ff(pr, fs, rhs0, QR, par, first);
     const unsigned act0 = ff.act0;
     double part[NR];
 #pragma unroll
@@ -862,7 +872,7 @@ __device__ __forceinline__ void phaseA_split_tile(const Prob &pr, int t, int par
     __shared__ FinShared<1> fs;
     int sb, rhs, d, i, s;
     split_tile(pr, KA, t, sb, rhs, d, i, s);
-    FusedFinish<1, true> ff(pr, fs, rhs, true, par, first);
+    FusedFinish<1, true, false> ff(pr, fs, rhs, true, par, first);
     const Geom g = pr.g;
     const int np = g.S[2];
     W *xy = (W *)lds;

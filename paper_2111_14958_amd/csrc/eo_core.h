@@ -109,7 +109,7 @@ __device__ __forceinline__ void eo_phaseA_tile(const Prob &pr, int t, int par = 
     int sb, grp, k;
     eo_tile<XY>(pr, KA, t, sb, grp, k);
     const int rhs0 = grp * NR;
-    FusedFinish<NR, true> ff(pr, fs, rhs0, QR, par, first);
+    FusedFinish<NR, true, false> ff(pr, fs, rhs0, QR, par, first);
     double part[NR];
 #pragma unroll
     for (int j = 0; j < NR; ++j) part[j] = 0.0;
