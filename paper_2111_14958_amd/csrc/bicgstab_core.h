@@ -62,8 +62,9 @@ struct alignas(16) BiRec {
     double wr, wi;   // omega
     double br, bi;   // beta
     double rh2, r2;  // |r_hat|^2, |r|^2
-    int state, iters, since_ru, restart;   // restart: the field restarts in this round of launches
+    int state, iters, since_ru;   // state: ST_*, or BI_RESTART in the round of launches that restarts the field
 };
+constexpr int BI_RESTART = 5;
 // columns of the fused iteration's partials: pr.part slots 0, 1 <r_hat, v>, 2
 // |r|^2; pr.part2 <t, s>, <t, t>, <r_hat, s>, <r_hat, t>
 constexpr int BI_R2 = 2, BI_NP2 = 7;
@@ -87,8 +88,9 @@ __device__ __forceinline__ double wave_col_sum(const double *col, int nsb) {
 __device__ __forceinline__ void bi_end(const Prob &pr, const BiRec &c, double stop2, double r2, BiRec &o) {
     o.ar = c.ar, o.ai = c.ai, o.wr = c.wr, o.wi = c.wi, o.br = c.br, o.bi = c.bi;
     o.rr = c.rr, o.ri = c.ri, o.rh2 = c.rh2, o.r2 = c.r2;
-    o.state = c.state, o.iters = c.iters, o.since_ru = c.since_ru, o.restart = 0;
-    if (o.state != ST_ACTIVE || c.restart) return;   // a restart is no iteration
+    o.state = c.state == BI_RESTART ? ST_ACTIVE : c.state;   // a restart is no iteration
+    o.iters = c.iters, o.since_ru = c.since_ru;
+    if (c.state != ST_ACTIVE) return;
     o.r2 = r2;
     o.iters += 1;
     o.since_ru += 1;
@@ -96,7 +98,7 @@ __device__ __forceinline__ void bi_end(const Prob &pr, const BiRec &c, double st
     else if (r2 <= stop2 || o.iters >= pr.max_iter || (pr.ru_every > 0 && o.since_ru >= pr.ru_every))
         o.state = ST_FROZEN;
     else if (o.rr * o.rr + o.ri * o.ri <= 1e-12 * o.rh2 * r2) {   // see bi5_finish
-        o.restart = 1;
+        o.state = BI_RESTART;
         o.rr = r2;
         o.ri = 0.0;
         o.rh2 = r2;
@@ -110,14 +112,16 @@ __device__ __forceinline__ void bi_end(const Prob &pr, const BiRec &c, double st
 template <int NR> struct BiBegin {
     const Prob &pr;
     const int rhs0, first;
-    unsigned act0;   // fields that iterate before this launch's finish
+    unsigned act0;   // fields that iterated before this launch's finish, or restarted
     double a[NR][4];
     __device__ __forceinline__ BiBegin(const Prob &p, int r0, int fi) : pr(p), rhs0(r0), first(fi) {
         act0 = 0;
 #pragma unroll
         for (int j = 0; j < NR; ++j)
-            if (rhs0 + j < pr.nrhs && (first ? pr.sc[rhs0 + j].state : pr.recm[rhs0 + j].state) == ST_ACTIVE)
-                act0 |= 1u << j;
+            if (rhs0 + j < pr.nrhs) {
+                const int st = first ? pr.sc[rhs0 + j].state : pr.recm[rhs0 + j].state;
+                if (st == ST_ACTIVE || st == BI_RESTART) act0 |= 1u << j;
+            }
     }
     __device__ __forceinline__ void begin() {
         if (!first && act0) col_issue<NR>(pr, rhs0, act0, a, BI_R2, pr.nsb[KS5]);
@@ -137,11 +141,11 @@ template <int NR> struct BiBegin {
                     o.rr = b.rho[0], o.ri = b.rho[1], o.ar = b.alpha[0], o.ai = b.alpha[1];
                     o.wr = b.omega[0], o.wi = b.omega[1], o.br = b.beta[0], o.bi = b.beta[1];
                     o.rh2 = b.rh2, o.r2 = c.rho;
-                    o.state = c.state, o.iters = c.iters, o.since_ru = c.since_ru, o.restart = 0;
+                    o.state = c.state, o.iters = c.iters, o.since_ru = c.since_ru;
                 } else {
                     bi_end(pr, pr.recm[i], pr.sc[i].stop2, act0 >> j & 1 ? r2[j] : 0.0, o);
                 }
-                go[j] = o.state == ST_ACTIVE && !o.restart;
+                go[j] = o.state == ST_ACTIVE;
                 if (sb == 0) pr.rec2[i] = o;
             }
         }
@@ -219,8 +223,7 @@ __device__ __forceinline__ void bi_stencil_tile(const Prob &pr, int t, int first
     if constexpr (F && S4) {
 #pragma unroll
         for (int j = 0; j < NR; ++j)
-            if (rhs0 + j < pr.nrhs && pr.rec3[rhs0 + j].state == ST_ACTIVE && !pr.rec3[rhs0 + j].restart)
-                act |= 1u << j;
+            if (rhs0 + j < pr.nrhs && pr.rec3[rhs0 + j].state == ST_ACTIVE) act |= 1u << j;
     } else if constexpr (F) {
         act = bb.act0;
         bb.begin();
@@ -359,7 +362,7 @@ __device__ __forceinline__ void bi3_tile(const Prob &pr, int t) {
         __shared__ double sum[2], al[2];
         __shared__ int go;
         const BiRec &c = pr.rec2[i];
-        const bool live = c.state == ST_ACTIVE && !c.restart;   // uniform over the block
+        const bool live = c.state == ST_ACTIVE;   // uniform over the block
         const int w = threadIdx.x >> 6;
         if (live && w < 2) {
             const double x = wave_col_sum(part_col(pr, i, w), pr.nsb[KS2]);
@@ -374,19 +377,20 @@ __device__ __forceinline__ void bi3_tile(const Prob &pr, int t) {
                 if (!dfinite(rv) || (rv.re == 0.0 && rv.im == 0.0)) state = ST_BREAKDOWN;
                 else na = ddiv(dc{c.rr, c.ri}, rv);
             }
-            go = live && state == ST_ACTIVE;
+            go = state;
             al[0] = na.re;
             al[1] = na.im;
             if (sb == 0) {
                 BiRec &o = pr.rec3[i];
                 o.rr = c.rr, o.ri = c.ri, o.ar = na.re, o.ai = na.im, o.wr = c.wr, o.wi = c.wi;
                 o.br = c.br, o.bi = c.bi, o.rh2 = c.rh2, o.r2 = c.r2;
-                o.state = state, o.iters = c.iters, o.since_ru = c.since_ru, o.restart = c.restart;
+                o.state = state, o.iters = c.iters, o.since_ru = c.since_ru;
             }
         }
         __syncthreads();
-        if (c.restart && s < pr.g.V) bi_restart<P>(pr, i, s);
-        if (!go || s >= pr.g.V) return;
+        if (s >= pr.g.V) return;
+        if (go == BI_RESTART) bi_restart<P>(pr, i, s);
+        if (go != ST_ACTIVE) return;
         a = dc{al[0], al[1]};
     } else {
         if (pr.sc[i].state != ST_ACTIVE || s >= pr.g.V) return;
@@ -460,7 +464,7 @@ __device__ __forceinline__ void bi5f_tile(const Prob &pr, int t) {
     __shared__ double sum[BI_NP2], sc[6];
     __shared__ int go;
     const BiRec &c = pr.rec3[i];
-    const bool live = c.state == ST_ACTIVE && !c.restart;   // uniform over the block
+    const bool live = c.state == ST_ACTIVE;   // uniform over the block
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     if (live)
         for (int k = w; k < BI_NP2; k += nw) {
@@ -481,13 +485,13 @@ __device__ __forceinline__ void bi5f_tile(const Prob &pr, int t) {
                 be = dmul(ddiv(rho, old), ddiv(al, om));
             }
         }
-        go = live && state == ST_ACTIVE;
+        go = state == ST_ACTIVE;
         sc[0] = al.re, sc[1] = al.im, sc[2] = om.re, sc[3] = om.im, sc[4] = be.re, sc[5] = be.im;
         if (sb == 0) {
             BiRec &o = pr.recm[i];
             o.rr = rho.re, o.ri = rho.im, o.ar = al.re, o.ai = al.im, o.wr = om.re, o.wi = om.im;
             o.br = be.re, o.bi = be.im, o.rh2 = c.rh2, o.r2 = c.r2;
-            o.state = state, o.iters = c.iters, o.since_ru = c.since_ru, o.restart = c.restart;
+            o.state = state, o.iters = c.iters, o.since_ru = c.since_ru;
         }
     }
     __syncthreads();
@@ -545,10 +549,11 @@ __device__ __forceinline__ void bi_trail_finish(const Prob &pr) {
     b.omega[0] = o.wr, b.omega[1] = o.wi, b.beta[0] = o.br, b.beta[1] = o.bi;
     b.rh2 = o.rh2;
     c.rho = o.r2;
-    c.state = o.state;
+    const bool restart = o.state == BI_RESTART;
+    c.state = restart ? ST_ACTIVE : o.state;
     c.iters = o.iters;
     c.since_ru = o.since_ru;
-    c.restart = c.pending_p = o.restart;
+    c.restart = c.pending_p = restart;
 }
 
 __device__ __forceinline__ void bi5_finish(const Prob &pr) {
