@@ -474,16 +474,18 @@ static void launch_split(const KindShape &k, hipStream_t st, const Prob *d, int 
     WD_TIMED_LAUNCH_LDS((k_phase_split<P, false, B>), gr, bl, k.lds, st, d, n, k.remap, par, edge);
 }
 
-// FP32 site blocks with x_lo updated in pairs (site_pair)
-template <bool B>
+// site blocks with x_lo updated in pairs (site_pair; FP64: nontemporal streams)
+template <int P, bool B>
 static void launch_pair(const KindShape &k, hipStream_t st, const Prob *d, int n, int par, int edge) {
     const dim3 gr(k.grid), bl(k.block);
     auto go = [&](auto a, auto b) {
         if (B) WD_TIMED_LAUNCH(b, gr, bl, st, d, n, k.remap, par, edge);
         else WD_TIMED_LAUNCH(a, gr, bl, st, d, n, k.remap, par, edge);
     };
-    if (k.r12) go(k_phaseA<P32, 1, 3, false, true, 0, false, true>, k_phaseB<P32, 1, 3, false, true, 0, false, true>);
-    else go(k_phaseA<P32, 1, 3, false, false, 0, false, true>, k_phaseB<P32, 1, 3, false, false, 0, false, true>);
+    constexpr int POL = P == P64 ? 1 : 0;
+    if (P == P32 && k.r12)
+        go(k_phaseA<P, 1, 3, false, P == P32, POL, false, true>, k_phaseB<P, 1, 3, false, P == P32, POL, false, true>);
+    else go(k_phaseA<P, 1, 3, false, false, POL, false, true>, k_phaseB<P, 1, 3, false, false, POL, false, true>);
 }
 
 template <int P>
@@ -493,7 +495,7 @@ static void launch_A(const KindShape &k, hipStream_t st, const Prob *d, int n, i
         return;
     }
     if (k.pair && !k.xy) {
-        launch_pair<false>(k, st, d, n, par, first);
+        launch_pair<P, false>(k, st, d, n, par, first);
         return;
     }
     if (k.ordered == 5) launch_AB_o5<P, false>(k, st, d, n, par, first);
@@ -508,7 +510,7 @@ static void launch_B(const KindShape &k, hipStream_t st, const Prob *d, int n, i
         return;
     }
     if (k.pair && !k.xy) {
-        launch_pair<true>(k, st, d, n, par, last);
+        launch_pair<P, true>(k, st, d, n, par, last);
         return;
     }
     if (k.ordered == 5) launch_AB_o5<P, true>(k, st, d, n, par, last);
@@ -937,7 +939,8 @@ void plan_shapes(const wd_gauge *g, int nrhs, int inner, LaunchSet &ls, Prob &pr
                 }
             }
             if ((k == KA || k == KB) && !pr.eo)
-                ks.pair = ks.xy == 1 || (ks.xy == 0 && site_pair(inner, ks.ordered, ks.nr, iterated));
+                ks.pair = ks.xy == 1 ||
+                          (ks.xy == 0 && site_pair(inner, ks.ordered, ks.nr, iterated, (int64_t)Vf * nrhs));
         } else {
             ks.block = 256;
             ks.nr = 1;

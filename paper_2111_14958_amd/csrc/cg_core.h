@@ -661,9 +661,7 @@ __device__ __forceinline__ void fa_reduce(const Prob &pr, int rhs0, unsigned act
 // 33.2 ms; a single 8^4 field, bound by latency, 2.08 -> 2.10 ms.  last = 1
 // (the chunk's last iteration): parity 0 adds its own alpha q at once.  A
 // field that freezes after a parity-0 iteration keeps its pending alpha q (xq
-// bit 1) for R1.  Plane blocks are paired; site blocks in FP32 while the fields
-// (one q more) stay in the L2s (site_pair), and not in FP64 and FP16N, where the
-// single update with q held in registers is the faster one.
+// bit 1) for R1.  Plane blocks are paired, site blocks by site_pair.
 template <int P, int NR, int ORD = 1, bool XY = false, bool R12 = false, int POL = 0, bool FA = false,
           bool MP = false, bool PAIR = XY>
 __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1, int last = 0) {
@@ -727,10 +725,12 @@ __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1,
                 for (int k = 0; k < 12; ++k) n += (double)norm2(r[k]);
                 part[j] = n;
                 if (!xup) continue;
-                // paired: issued once r is done with (no instruction): three more
+                // LATE: issued once r is done with (no instruction): three more
                 // spinors loaded ahead of it would cost phase B a wave per SIMD
+                // (FP64 site blocks have waves to spare, see phase_waves)
+                constexpr bool LATE = PAIR && (XY || P != P64);
                 int sx = s;
-                if constexpr (PAIR) asm volatile("" : "+v"(sx) : "v"(n));
+                if constexpr (LATE) asm volatile("" : "+v"(sx) : "v"(n));
                 cx<RX> x[12];
                 Spinor<XP>::template load<POL>(fx, rhs0 + j, sx, x);
                 if (PAIR && par > 0) {   // the iteration before's update first
@@ -741,7 +741,7 @@ __device__ __forceinline__ void phaseB_tile(const Prob &pr, int t, int par = -1,
 #pragma unroll
                     for (int k = 0; k < 12; ++k) x[k] = {x[k].re + ao * (RX)qo[k].re, x[k].im + ao * (RX)qo[k].im};
                 }
-                if constexpr (PAIR) {   // q read again (from LDS, or a line this thread has just
+                if constexpr (LATE) {   // q read again (from LDS, or a line this thread has just
                                         // read), so that it is not held meanwhile
                     int tx = XY ? (int)threadIdx.x : sx;
                     asm volatile("" : "+v"(tx) : "v"(x[0].re), "v"(x[11].im));

@@ -49,15 +49,23 @@ struct WsLayout {
     size_t total;
 };
 
-// Site-blocked phases A and B that update x_lo in pairs: FP32 with two hops in
-// flight and one rhs per thread, while r, q in two buffers and x_lo (bytes) fit
-// three quarters of the eight 4 MB L2s.  Whole solves, single against paired: 8 x
-// 4 x 16 x 16 x 6 (18.9 MB) 3.44 -> 3.33 ms, 6 x 8 x 8 x 8 x 3 2.64 -> 2.59; but 7 x 7
-// x 14 x 14 x 8 (29.5 MB) 4.36 -> 4.43, 4 x 14 x 12 x 14 x 12 (43 MB) 4.79 -> 4.87, 16
-// x 3 x 32 x 24 x 4 (57 MB) 6.54 -> 6.77 ms.  FP64 at these sizes 4.62 -> 4.93, 3.17
-// -> 3.18, 7.97 -> 8.13, 8.58 -> 8.77, 12.69 -> 12.81; FP16N within 1 % of each other.
-inline int site_pair(int prec, int ordered, int nr, size_t bytes) {
-    return prec == WD_F32 && ordered == 3 && nr == 1 && bytes <= (size_t)24 << 20;
+// Do site-blocked phases A and B (two hops in flight, one rhs per thread) update
+// x_lo in pairs?  bytes: r, q in two buffers and x_lo; threads: sites times fields.
+// Whole solves, single against paired:
+// FP32: while bytes fit three quarters of the eight 4 MB L2s.  8 x 4 x 16 x 16 x 6
+// (18.9 MB) 3.44 -> 3.33 ms, 6 x 8 x 8 x 8 x 3 2.64 -> 2.59; but 7 x 7 x 14 x 14 x 8
+// (29.5 MB) 4.36 -> 4.43, 16 x 3 x 32 x 24 x 4 (57 MB) 6.54 -> 6.77, 7 x 8 x 16 x 32 x 12
+// (126 MB) 12.44 -> 12.66 ms.
+// FP64: beyond the MALL.  5 x 12 x 16 x 32 x 16 (360 MB) 34.6 -> 34.0, 4 x 15 x 16 x 32 x
+// 12 (270 MB) 27.3 -> 26.8; but 7 x 8 x 16 x 32 x 12 (252 MB) 24.4 -> 25.1, 8 x 4 x 16 x
+// 16 x 6 4.62 -> 4.93 ms.
+// FP16N: where the single kernel (82 VGPRs, five blocks per compute unit) no longer
+// runs in one round of 256 x 5 blocks of 256; the paired one has four.  14^4 x 9 9.20
+// -> 9.00, 14^4 x 16 13.89 -> 13.52, 8 x 8 x 16 x 32 x 12 10.39 -> 10.01; but 8 x 8 x 16 x
+// 32 x 10 (1280 blocks) 8.70 -> 9.01, 12^4 x 15 7.74 -> 7.92, 12^4 x 4 4.04 -> 4.11 ms.
+inline int site_pair(int prec, int ordered, int nr, size_t bytes, int64_t threads) {
+    if (ordered != 3 || nr != 1) return 0;
+    return prec == WD_F32 ? bytes <= (size_t)24 << 20 : prec == WD_F64 ? bytes > (size_t)256 << 20 : threads > 327680;
 }
 // LDS bytes of a direction-split block: the staged plane of np sites and the
 // sums' two buffers (24 reals per site each)

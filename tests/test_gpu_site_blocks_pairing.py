@@ -1,8 +1,9 @@
 """Where site-blocked CG phases update x_lo in pairs of iterations: FP32 while r, the
-two q buffers and x_lo fit 24 MB (65536 sites times fields), and not FP64 or FP16N.
+two q buffers and x_lo fit 24 MB (65536 sites times fields), FP64 beyond 256 MB
+(349525), FP16N beyond 327680 sites times fields.
 Paired or single, fused finish or separate launches, the arithmetic is the same:
 the solutions and reports equal those of WD_CG_UNFUSED=1 bit for bit, on both sides
-of the limit and with shapes set for one phase only (which run the separate
+of each limit and with shapes set for one phase only (which run the separate
 launches where the phases would pair differently).  Chunks of 7 iterations and
 reliable updates after 9 cut pairs in half."""
 import os
@@ -39,8 +40,8 @@ def _check(U, eta, dims, inner, **kw):
 
 
 @pytest.mark.parametrize("inner", [wd.F64, wd.F32, wd.F16N], ids=["f64", "f32", "f16n"])
-@pytest.mark.parametrize("nrhs", [6, 7])     # 9408 sites: 56448 and 65856
-def test_both_sides_of_the_limit(nrhs, inner):
+@pytest.mark.parametrize("nrhs", [6, 7, 34, 35, 37, 38])   # 9408 sites: 56448, 65856; 319872, 329280; 348096, 357504
+def test_both_sides_of_the_limits(nrhs, inner):
     dims = (4, 14, 12, 14)
     U = wdgen.gauge_field(dims, 0.4, 6000)
     eta = wdgen.gaussian_source(dims, nrhs, 6001)
